@@ -95,10 +95,10 @@ constexpr int64_t halo_buffer_words(int64_t n) {
                           : (n / 8) * (n / 4) * (n / 4) * halo_words<8, 4, 4>() + 64;
 }
 
-// A thread forms its cell's 81 results one input component at a time
-// (cellop::apply_cell_by_input): 27 inputs live beside the 81 results, 128
-// VGPRs in FP32 (four waves per SIMD; three when accumulating, whose old
-// values need more) and 254 in FP64 (two waves per SIMD).
+// A thread holds its cell's 81 values and turns them into the 81 results in
+// place (cellop::apply_cell): 126 VGPRs in FP32 (four waves per SIMD; three
+// when accumulating, whose old values need more) and 233 in FP64 (two waves
+// per SIMD).
 template <typename T, bool ACC>
 constexpr int brick_waves_per_simd() {
   return sizeof(T) == 4 ? (ACC ? 3 : 4) : 2;
@@ -179,24 +179,22 @@ __global__ __launch_bounds__(BX * BY * BZ, (brick_waves_per_simd<T, ACC>())) voi
     for (int e = t; e < NV; e += NT) b4[e] = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int e = NV * 16 / int(sizeof(T)) + t; e < 3 * CS; e += NT) buf[e] = T(0);
   };
-  // the cell's results, one input component at a time from the box; then
-  // the box is zeroed and takes the sums
+  // the cell's results (without mu h); then the box is zeroed and takes the sums
   T U[3][27];
   const T mu_h = mu[cell] / T(n);
-  cellop::apply_cell_by_input<T>(
-      [&](int q, T(&V)[27]) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c)
+  for (int q = 0; q < 3; ++q)
 #pragma unroll
-          for (int bb = 0; bb < 3; ++bb)
+    for (int c = 0; c < 3; ++c)
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-              const int off = split_index<BZ>(2 * cz + c) * PL + split_index<BY>(2 * cy + bb) * RX +
-                              split_index<BX>(2 * cx + a);
-              V[a + 3 * bb + 9 * c] = buf[q * CS + off];
-            }
-      },
-      U, mu_h);
+      for (int bb = 0; bb < 3; ++bb)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const int off =
+              split_index<BZ>(2 * cz + c) * PL + split_index<BY>(2 * cy + bb) * RX + split_index<BX>(2 * cx + a);
+          U[q][a + 3 * bb + 9 * c] = buf[q * CS + off];
+        }
+  cellop::apply_cell(U);
   __syncthreads();
   zero_box();
   __syncthreads();
@@ -228,7 +226,7 @@ __global__ __launch_bounds__(BX * BY * BZ, (brick_waves_per_simd<T, ACC>())) voi
           for (int a = ac ? 2 : 0; a < (ac ? 3 : 2); ++a) {
             const int off = split_index<BZ>(2 * cz + c) * PL + split_index<BY>(2 * cy + bb) * RX + split_index<BX>(2 * cx + a);
 #pragma unroll
-            for (int q = 0; q < 3; ++q) buf[q * CS + off] = tmp[q][c & 1][bb & 1][a & 1] + U[q][a + 3 * bb + 9 * c];
+            for (int q = 0; q < 3; ++q) buf[q * CS + off] = tmp[q][c & 1][bb & 1][a & 1] + mu_h * U[q][a + 3 * bb + 9 * c];
           }
       __builtin_amdgcn_s_waitcnt(0xc07f);
       asm volatile("" ::: "memory");

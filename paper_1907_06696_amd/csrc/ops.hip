@@ -105,8 +105,9 @@ __global__ __launch_bounds__(256) void k_init_out_general(int64_t nn, const uint
 // and the time is the per-thread chain of the cell operator, about 2.5x
 // shorter than with one thread per cell.
 // Block: 64 cells x 3 components (wave c holds component c); each thread
-// interpolates its component to the Gauss points, the 81 values are shared
-// through LDS, and each thread produces its component's 27 outputs.
+// transforms its component to modes, the 81 modes are shared through LDS, and
+// each thread produces its component's 27 outputs from its own modes and the
+// 24 of the other components that couple to them.
 template <typename T>
 __global__ __launch_bounds__(192) void k_vmult_uniform3(int64_t n, const T* __restrict__ mu, const T* __restrict__ x,
                                                         T* __restrict__ y) {
@@ -126,20 +127,17 @@ __global__ __launch_bounds__(192) void k_vmult_uniform3(int64_t n, const T* __re
         const int32_t sl = uc.slot(xx, yy, z);
         w[xx + 3 * yy + 9 * z] = sl >= 0 ? x[3 * int64_t(sl) + c] : T(0);
       }
-  cellop::interp_all(w);
+  const T mu_h = mu[live ? cell : 0] / T(n);
+  cellop::modes_all(w);
 #pragma unroll
   for (int a = 0; a < 27; ++a) wsh[c][a][lane] = w[a];
   __syncthreads();
-  T W[3][27];
+  auto modes = [&](int d, int j) { return wsh[d][j][lane]; };
+  if (c == 0) cellop::apply_component<0>(w, modes);
+  else if (c == 1) cellop::apply_component<1>(w, modes);
+  else cellop::apply_component<2>(w, modes);
 #pragma unroll
-  for (int cc = 0; cc < 3; ++cc)
-#pragma unroll
-    for (int a = 0; a < 27; ++a) W[cc][a] = wsh[cc][a][lane];
-  const T mu_h = mu[live ? cell : 0] / T(n);
-  if (c == 0) cellop::apply_cell_row<0>(W, w, mu_h);
-  else if (c == 1) cellop::apply_cell_row<1>(W, w, mu_h);
-  else cellop::apply_cell_row<2>(W, w, mu_h);
-  cellop::interp_all_t(w);
+  for (int a = 0; a < 27; ++a) w[a] *= mu_h;
   // A cell's xx = 2 nodes are the next cell's xx = 0 nodes.  Within a row of
   // 16 lanes the next cell along x is the next lane, which adds the values
   // passed on (DPP row shift) into its own: those nodes take one atomic
@@ -227,8 +225,8 @@ double* face_slots<double>(const DevLevel& L) {
 // operator with three threads per cell, one velocity component each (a wave
 // per component, as k_vmult_uniform3), hanging nodes resolved through the
 // level's constraint rows (HANG).  A thread gathers,
-// interpolates and scatters its component's 27 values and computes its
-// component's row of the cell operator from all three interpolated
+// transforms and scatters its component's 27 values and computes its
+// component's rows of the cell operator from the modes of all three
 // components, exchanged through LDS.  The single cells are few, so the kernel
 // is latency-bound; this cuts each thread's chain of dependent loads,
 // arithmetic and atomics to about a third.
@@ -282,20 +280,17 @@ __global__ __launch_bounds__(192) void k_vmult_general3(const int32_t* __restric
     else
       w[a] = sl[a] >= 0 && !slot_fixed(sl[a], comp) ? x[3 * int64_t(slot_node(sl[a])) + comp] : T(0);
   }
-  cellop::interp_all(w);
+  const T mu_h = mu[c] * T(ldexp(1.0, -int(clev[c])));
+  cellop::modes_all(w);
 #pragma unroll
   for (int a = 0; a < 27; ++a) wsh[comp][a][lane] = w[a];
   __syncthreads();
-  T W[3][27];
+  auto modes = [&](int d, int j) { return wsh[d][j][lane]; };
+  if (comp == 0) cellop::apply_component<0>(w, modes);
+  else if (comp == 1) cellop::apply_component<1>(w, modes);
+  else cellop::apply_component<2>(w, modes);
 #pragma unroll
-  for (int cc = 0; cc < 3; ++cc)
-#pragma unroll
-    for (int a = 0; a < 27; ++a) W[cc][a] = wsh[cc][a][lane];
-  const T mu_h = mu[c] * T(ldexp(1.0, -int(clev[c])));
-  if (comp == 0) cellop::apply_cell_row<0>(W, w, mu_h);
-  else if (comp == 1) cellop::apply_cell_row<1>(W, w, mu_h);
-  else cellop::apply_cell_row<2>(W, w, mu_h);
-  cellop::interp_all_t(w);
+  for (int a = 0; a < 27; ++a) w[a] *= mu_h;
   if (!live) return;
 #pragma unroll
   for (int a = 0; a < 27; ++a) {
@@ -449,7 +444,7 @@ __global__ __launch_bounds__(64) void k_vmult_blocks(DevBlocks blk, const int8_t
     const int32_t c = blk.cells[(blk0 + bl) * NC + lc];
     coef = mu[c] * T(ldexp(1.0, -int(clev[c])));
   }
-  cellop::apply_cell<T>(U, coef);
+  cellop::apply_cell(U);
   __syncthreads();
 #pragma unroll
   for (int cls = 0; cls < 8; ++cls) {
@@ -462,7 +457,7 @@ __global__ __launch_bounds__(64) void k_vmult_blocks(DevBlocks blk, const int8_t
         for (int xx = ac ? 2 : 0; xx < (ac ? 3 : 2); ++xx) {
           const int off = base + bsplit<B>(2 * ca + xx) + E * bsplit<B>(2 * cb + yy) + E * E * bsplit<B>(2 * cc + z);
 #pragma unroll
-          for (int q = 0; q < 3; ++q) buf[off + q * P] += U[q][xx + 3 * yy + 9 * z];
+          for (int q = 0; q < 3; ++q) buf[off + q * P] += coef * U[q][xx + 3 * yy + 9 * z];
         }
     __syncthreads();
   }
@@ -1228,21 +1223,18 @@ __global__ __launch_bounds__(256) void k_vcycle_tail(const T* __restrict__ mu, c
             const T v = xs[3 * max(sl, 0) + c];   // every read issued, the Dirichlet ones dropped
             w[xx + 3 * yy + 9 * z] = sl >= 0 ? v : T(0);
           }
-      cellop::interp_all(w);
+      cellop::modes_all(w);
 #pragma unroll
       for (int a = 0; a < 27; ++a) wsh[c][a][cell] = w[a];
     }
     __syncthreads();
     if (opt) {
-      T W[3][27];
+      auto modes = [&](int d, int j) { return wsh[d][j][cell]; };
+      if (c == 0) cellop::apply_component<0>(w, modes);
+      else if (c == 1) cellop::apply_component<1>(w, modes);
+      else cellop::apply_component<2>(w, modes);
 #pragma unroll
-      for (int cc = 0; cc < 3; ++cc)
-#pragma unroll
-        for (int a = 0; a < 27; ++a) W[cc][a] = wsh[cc][a][cell];
-      if (c == 0) cellop::apply_cell_row<0>(W, w, mu_h);
-      else if (c == 1) cellop::apply_cell_row<1>(W, w, mu_h);
-      else cellop::apply_cell_row<2>(W, w, mu_h);
-      cellop::interp_all_t(w);
+      for (int a = 0; a < 27; ++a) w[a] *= mu_h;
       if constexpr (sizeof(T) == 8) {   // FP64: LDS atomics (the ordered form below spills here)
 #pragma unroll
         for (int z = 0; z < 3; ++z)
