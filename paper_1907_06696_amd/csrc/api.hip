@@ -794,30 +794,43 @@ void smooth_on(mfgmg_ctx* ctx, LevelDev& d, const T* b, T* x, bool x_zero, hipSt
   const double lam = sc ? d.lambda_s : d.lambda, lo = lam / 15.0;
   const double theta = 0.5 * (lam + lo), delta = 0.5 * (lam - lo), sigma = theta / delta;
   double rho = 1.0 / sigma;
+  double alpha[4] = {0.0}, beta[4] = {1.0 / theta};
+  for (int k = 1; k < 4; ++k) {
+    const double rho_new = 1.0 / (2.0 * sigma - rho);
+    alpha[k] = rho_new * rho;
+    beta[k] = 2.0 * rho_new / delta;
+    rho = rho_new;
+  }
+  if (smoother_fuses(d.v)) {   // x and t take turns; the last step writes x
+    if (x_zero) {
+      launch_fused_first<T>(d.v, b, minv, dd, x, beta[0], alpha[1], beta[1], s);
+    } else {
+      launch_fused_step<T>(d.v, x, b, minv, dd, t, alpha[0], beta[0], false, s);
+      launch_fused_step<T>(d.v, t, b, minv, dd, x, alpha[1], beta[1], false, s);
+    }
+    launch_fused_step<T>(d.v, x, b, minv, dd, t, alpha[2], beta[2], false, s);
+    launch_fused_step<T>(d.v, t, b, minv, dd, x, alpha[3], beta[3], true, s);
+    return;
+  }
   // where the operator starts with an output initialisation kernel, each
   // update prepares t for the next operator call on x instead (after the last
   // update of a pre-smoothing, for the V-cycle's residual)
-  const bool prep = vmult_has_init<T>(d.v);
+  const bool prep = vmult_has_init(d.v);
   ChebPrep cp;
   if (prep) {
     cp.tn = t;
-    cp.cmask = d.v.uniform ? nullptr : d.v.cmask;
-    cp.m = d.v.uniform ? 2 * d.v.n_edge + 1 : 0;
-    cp.from_x = true;
+    cp.cmask = d.v.cmask;
   }
   if (x_zero) {
-    launch_chebx_init0<T>(n, b, minv, dd, x, 1.0 / theta, s, cp);
+    launch_chebx_init0<T>(n, b, minv, dd, x, beta[0], s, cp);
   } else {
     launch_vmult<T>(d.v, x, t, s);
-    launch_chebx_step<T>(n, b, t, minv, dd, x, 0.0, 1.0 / theta, s, cp);
+    launch_chebx_step<T>(n, b, t, minv, dd, x, alpha[0], beta[0], s, cp);
   }
   for (int k = 1; k < 4; ++k) {
     if (prep) launch_vmult_prepared<T>(d.v, x, t, s);
     else launch_vmult<T>(d.v, x, t, s);
-    const double rho_new = 1.0 / (2.0 * sigma - rho);
-    launch_chebx_step<T>(n, b, t, minv, dd, x, rho_new * rho, 2.0 * rho_new / delta, s,
-                         k < 3 || x_zero ? cp : ChebPrep());
-    rho = rho_new;
+    launch_chebx_step<T>(n, b, t, minv, dd, x, alpha[k], beta[k], s, k < 3 || x_zero ? cp : ChebPrep());
   }
 }
 
@@ -851,11 +864,17 @@ void vcycle(mfgmg_ctx* ctx, int ell, const T* b, T* x, hipStream_t s) {
   T* bc = static_cast<T*>(c.work[pi][0]);
   T* xc = static_cast<T*>(c.work[pi][1]);
   smooth<T>(ctx, ell, b, x, true, s);
-  // the pre-smoothing left t prepared for A x where the operator needs it
-  if (vmult_has_init<T>(d.v)) launch_vmult_prepared<T>(d.v, x, t, s);
-  else launch_vmult<T>(d.v, x, t, s);
+  const T *rb = b, *rt = t;   // the residual is rb - rt
+  if (smoother_fuses(d.v)) {
+    launch_fused_residual<T>(d.v, x, b, t, s);
+    rb = t, rt = nullptr;
+  } else if (vmult_has_init(d.v)) {   // the pre-smoothing left t prepared for A x
+    launch_vmult_prepared<T>(d.v, x, t, s);
+  } else {
+    launch_vmult<T>(d.v, x, t, s);
+  }
   // the smoother's r and d are free here: scratch of the restriction passes
-  launch_restrict_level<T>(d.v, c.v, d.R_ptr, d.R_col, d.R_w, b, t, bc, static_cast<T*>(d.work[pi][2]),
+  launch_restrict_level<T>(d.v, c.v, d.R_ptr, d.R_col, d.R_w, rb, rt, bc, static_cast<T*>(d.work[pi][2]),
                            static_cast<T*>(d.work[pi][3]), s);
   vcycle<T>(ctx, ell - 1, bc, xc, s);
   launch_prolong_level<T>(d.v, c.v, d.P_ptr, d.P_col, d.P_w, xc, x, true, s);

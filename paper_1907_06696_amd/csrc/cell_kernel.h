@@ -161,13 +161,42 @@ __device__ __forceinline__ void apply_cell(T (&U)[3][27]) {
 
 // Component C of K_hat U where one thread holds one component: w, this
 // component's modes (modes_all applied), on return its nodal results; modes
-// of the other components are fetched with get(component, mode) (24 of them).
+// of the other components are fetched with get(component, mode) (24 of them;
+// both arguments are integral constants).
+// Of a component's modes the other components read 16: those at most linear
+// along the component's own axis and not constant along both others.
+// mode_slot: a mode's rank among them (-1: not read).
+constexpr int kSharedModes = 16;
+constexpr bool mode_shared(int c, int i) {
+  return mode_axis(i, c) < 2 && (mode_axis(i, (c + 1) % 3) > 0 || mode_axis(i, (c + 2) % 3) > 0);
+}
+constexpr int mode_slot(int c, int i) {
+  if (!mode_shared(c, i)) return -1;
+  int s = 0;
+  for (int j = 0; j < i; ++j) s += mode_shared(c, j) ? 1 : 0;
+  return s;
+}
+
+// put(slot, value) for the modes of component C that the others read
+template <int C, int I, typename T, typename Put>
+__device__ __forceinline__ void share_mode(const T (&w)[27], const Put& put) {
+  if constexpr (mode_shared(C, I)) put(mode_slot(C, I), w[I]);
+}
+template <int C, typename T, typename Put, int... I>
+__device__ __forceinline__ void share_modes(const T (&w)[27], const Put& put, std::integer_sequence<int, I...>) {
+  (share_mode<C, I>(w, put), ...);
+}
+template <int C, typename T, typename Put>
+__device__ __forceinline__ void share_modes(const T (&w)[27], const Put& put) {
+  share_modes<C>(w, put, std::make_integer_sequence<int, 27>());
+}
+
 template <int C, typename T, typename Get, int... I>
 __device__ __forceinline__ void component_rows(T (&w)[27], const Get& get, std::integer_sequence<int, I...>) {
   T r[27];
   ((r[I] = mode_row<C, I, T>([&](auto d, auto j) {
       if constexpr (decltype(d)::value == C) return w[decltype(j)::value];
-      else return get(decltype(d)::value, decltype(j)::value);
+      else return get(d, j);
     })), ...);
   ((w[I] = r[I]), ...);
 }

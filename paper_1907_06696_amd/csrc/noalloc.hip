@@ -1,8 +1,9 @@
 // The Q2 strain-rate operator on a uniform mesh without any allocation:
 // mfgmg_vmult_uniform_noalloc (declared in include/mfgmg.h).
 //
-// The brick operator of a uniform level needs, besides x, y and the cell
-// viscosity, its halo slots: per brick the contributions to the nodes of its
+// The brick operator of a uniform level (FP64, and FP32 at 64^3; FP32 at 32^3
+// runs the owner kernel, which needs none of this) needs, besides x, y and the
+// cell viscosity, its halo slots: per brick the contributions to the nodes of its
 // upper neighbours, written by the brick kernel and added by the halo kernel,
 // plus a zero pad that the halo kernel reads in place of slots that do not
 // apply.  Here those slots live in one file-scope device array, `scratch`,
@@ -106,23 +107,27 @@ extern "C" int mfgmg_vmult_uniform_noalloc(int32_t n_edge, mfgmg_prec prec, cons
   v.nnode = (2 * n + 1) * (2 * n + 1) * (2 * n + 1);
   if (prec == MFGMG_FP64) {
     const int64_t words = brick_halo_words<double>(n);
-    if (words <= 64 || words * int64_t(sizeof(double)) > kScratchBytes) {
+    if (words * int64_t(sizeof(double)) > kScratchBytes) {
       g_last_error = "halo slots exceed the scratch array";
       return MFGMG_ERR_INVALID;
     }
     v.mu_d = static_cast<const double*>(mu);
-    v.halo_d = static_cast<double*>(base);
-    launch_fill(64, 0.0, v.halo_d + (words - 64), s);
+    if (words > 64) {   // 0: this size and precision run without halo slots
+      v.halo_d = static_cast<double*>(base);
+      launch_fill(64, 0.0, v.halo_d + (words - 64), s);
+    }
     launch_vmult<double>(v, static_cast<const double*>(src), static_cast<double*>(dst), s, true);
   } else {
     const int64_t words = brick_halo_words<float>(n);
-    if (words <= 64 || words * int64_t(sizeof(float)) > kScratchBytes) {
+    if (words * int64_t(sizeof(float)) > kScratchBytes) {
       g_last_error = "halo slots exceed the scratch array";
       return MFGMG_ERR_INVALID;
     }
     v.mu_f = static_cast<const float*>(mu);
-    v.halo_f = static_cast<float*>(base);
-    launch_fill_f(64, 0.0f, v.halo_f + (words - 64), s);
+    if (words > 64) {   // 0: this size and precision run without halo slots
+      v.halo_f = static_cast<float*>(base);
+      launch_fill_f(64, 0.0f, v.halo_f + (words - 64), s);
+    }
     launch_vmult<float>(v, static_cast<const float*>(src), static_cast<float*>(dst), s, true);
   }
   const hipError_t rc = hipGetLastError();

@@ -164,34 +164,43 @@ void launch_cheb_step(int64_t n, const T* t, const T* minv, T* r, T* d, T* x, do
                       hipStream_t s);
 // With p.tn set, the smoother's updates (launch_chebx_*) also prepare the
 // output of the next operator call on a level whose operator starts with an
-// initialisation kernel: tn = (constrained ? src : 0), src the new x (from_x)
-// or the new d; that call is then launch_vmult_prepared.  cmask: the level's
-// constrained-component masks (general levels), else null and m = 2n + 1
-// (uniform levels).
+// initialisation kernel: tn = (constrained ? the new x : 0); that call is then
+// launch_vmult_prepared.  cmask: the level's constrained-component masks.
 struct ChebPrep {
   void* tn = nullptr;
   const uint8_t* cmask = nullptr;
-  int64_t m = 0;
-  bool from_x = false;
 };
 // the smoother's form (residual b - A x formed each step, r not stored):
 // init0 from x = 0; step: d = alpha d + beta minv (b - t), x += d (alpha = 0:
-// d is not read).  p prepares t for the next operator call on x (from_x).
+// d is not read).  p prepares t for the next operator call on x.
 template <typename T>
 void launch_chebx_init0(int64_t n, const T* b, const T* minv, T* d, T* x, double inv_theta, hipStream_t s,
                         const ChebPrep& p = ChebPrep());
 template <typename T>
 void launch_chebx_step(int64_t n, const T* b, const T* t, const T* minv, T* d, T* x, double alpha, double beta,
                        hipStream_t s, const ChebPrep& p = ChebPrep());
-// true when launch_vmult<T> on L starts with an output initialisation kernel
-// (every level but the uniform ones the brick kernel takes and the Q3 lattice
-// levels)
-template <typename T>
+// true when launch_vmult on L starts with an output initialisation kernel
+// (the general levels)
 bool vmult_has_init(const DevLevel& L);
 // y = A x like launch_vmult (init), for a y already holding x on the
 // constrained dofs and 0 elsewhere (the initialisation kernel is skipped)
 template <typename T>
 void launch_vmult_prepared(const DevLevel& L, const T* x, T* y, hipStream_t s);
+
+// Uniform levels up to 32^3 cells: the smoother's update and the residual
+// formed inside the operator's kernel.  y must be neither x nor b.
+//   first: x0 = d0 = it0 minv b (not stored), then d = alpha d0 + beta minv
+//   (b - A x0), y = x0 + d; step: d = alpha d + beta minv (b - A x), y = x + d
+//   (alpha = 0: d is not read; last: d is not stored); residual: y = b - A x
+bool smoother_fuses(const DevLevel& L);
+template <typename T>
+void launch_fused_first(const DevLevel& L, const T* b, const T* minv, T* d, T* y, double it0, double alpha,
+                        double beta, hipStream_t s);
+template <typename T>
+void launch_fused_step(const DevLevel& L, const T* x, const T* b, const T* minv, T* d, T* y, double alpha, double beta,
+                       bool last, hipStream_t s);
+template <typename T>
+void launch_fused_residual(const DevLevel& L, const T* x, const T* b, T* y, hipStream_t s);
 
 // transfers (node-level CSR, 3 components).  cm_fine / cm_coarse (may be
 // null): constrained-component masks of the two levels; a masked component

@@ -6,6 +6,7 @@
 
 #include "brick_kernel.h"
 #include "cell_kernel.h"
+#include "owner_kernel.h"
 
 namespace mfgmg {
 
@@ -22,10 +23,7 @@ constexpr int kRedBlocks = 1024;   // partial sums of the reductions
 #endif
 constexpr int kRestrictLanes = MFGMG_RESTRICT_LANES;   // lanes per row of the CSR transfers
 constexpr int kProlongLanes = MFGMG_PROLONG_LANES;
-#ifndef MFGMG_BRICK_MIN_EDGE
-#define MFGMG_BRICK_MIN_EDGE 32
-#endif
-constexpr int64_t kBrickMinEdge = MFGMG_BRICK_MIN_EDGE;   // smallest uniform level using the brick kernel
+constexpr int64_t kFusedMaxEdge = 32;   // largest uniform level whose smoother is fused with its operator
 
 __constant__ double c_khat_diag[81];
 __constant__ double c_bhat[8 * 81];
@@ -62,33 +60,7 @@ struct UniformCell {
   }
 };
 
-// The value of lane - 1 within the lane's row of 16 lanes (DPP row shift
-// right by one; 0 at a row's first lane)
-__device__ __forceinline__ int dpp_from_left(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);
-}
-__device__ __forceinline__ float from_left_lane(float v) {
-  return __int_as_float(dpp_from_left(__float_as_int(v)));
-}
-__device__ __forceinline__ double from_left_lane(double v) {
-  const long long b = __double_as_longlong(v);
-  const unsigned lo = unsigned(dpp_from_left(int(b))), hi = unsigned(dpp_from_left(int(b >> 32)));
-  return __longlong_as_double(static_cast<long long>((static_cast<unsigned long long>(hi) << 32) | lo));
-}
-
 // ------------------------------------------------------------- vmult
-template <typename T>
-__global__ __launch_bounds__(256) void k_init_out_uniform(int64_t n, const T* __restrict__ x, T* __restrict__ y) {
-  const int64_t m = 2 * n + 1, nn = m * m * m;
-  for (int64_t v = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; v < nn; v += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t X = v % m, Y = (v / m) % m, Z = v / (m * m);
-    const bool b = X == 0 || Y == 0 || Z == 0 || X == m - 1 || Y == m - 1 || Z == m - 1;
-    y[3 * v] = b ? x[3 * v] : T(0);
-    y[3 * v + 1] = b ? x[3 * v + 1] : T(0);
-    y[3 * v + 2] = b ? x[3 * v + 2] : T(0);
-  }
-}
-
 template <typename T>
 __global__ __launch_bounds__(256) void k_init_out_general(int64_t nn, const uint8_t* __restrict__ cmask,
                                                           const T* __restrict__ x, T* __restrict__ y) {
@@ -98,84 +70,6 @@ __global__ __launch_bounds__(256) void k_init_out_general(int64_t nn, const uint
     y[3 * v + 1] = (b & 2) ? x[3 * v + 1] : T(0);
     y[3 * v + 2] = (b & 4) ? x[3 * v + 2] : T(0);
   }
-}
-
-// The operator on a uniform level below the brick kernel's sizes, three
-// threads per cell, one per output component: there the grid is a few waves
-// and the time is the per-thread chain of the cell operator, about 2.5x
-// shorter than with one thread per cell.
-// Block: 64 cells x 3 components (wave c holds component c); each thread
-// transforms its component to modes, the 81 modes are shared through LDS, and
-// each thread produces its component's 27 outputs from its own modes and the
-// 24 of the other components that couple to them.
-template <typename T>
-__global__ __launch_bounds__(192) void k_vmult_uniform3(int64_t n, const T* __restrict__ mu, const T* __restrict__ x,
-                                                        T* __restrict__ y) {
-  __shared__ T wsh[3][27][64];
-  const int lane = threadIdx.x & 63;
-  const int c = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-  const int64_t cell = blockIdx.x * int64_t(64) + lane;
-  const bool live = cell < n * n * n;
-  const UniformCell uc(n, live ? cell : 0);
-  T w[27];
-#pragma unroll
-  for (int z = 0; z < 3; ++z)
-#pragma unroll
-    for (int yy = 0; yy < 3; ++yy)
-#pragma unroll
-      for (int xx = 0; xx < 3; ++xx) {
-        const int32_t sl = uc.slot(xx, yy, z);
-        w[xx + 3 * yy + 9 * z] = sl >= 0 ? x[3 * int64_t(sl) + c] : T(0);
-      }
-  const T mu_h = mu[live ? cell : 0] / T(n);
-  cellop::modes_all(w);
-#pragma unroll
-  for (int a = 0; a < 27; ++a) wsh[c][a][lane] = w[a];
-  __syncthreads();
-  auto modes = [&](int d, int j) { return wsh[d][j][lane]; };
-  if (c == 0) cellop::apply_component<0>(w, modes);
-  else if (c == 1) cellop::apply_component<1>(w, modes);
-  else cellop::apply_component<2>(w, modes);
-#pragma unroll
-  for (int a = 0; a < 27; ++a) w[a] *= mu_h;
-  // A cell's xx = 2 nodes are the next cell's xx = 0 nodes.  Within a row of
-  // 16 lanes the next cell along x is the next lane, which adds the values
-  // passed on (DPP row shift) into its own: those nodes take one atomic
-  // instead of two (device-scope atomics, served beyond the XCD's L2, are most
-  // of this kernel's time on a 16^3 level).
-  // The same along y: the next cell along y is lane + n (when still in the
-  // block), which takes the yy = 2 row of values (those not already passed on
-  // along x) into its yy = 0 row.
-  const int64_t cc0 = live ? cell : 0;
-  const int ix = int(cc0 % n), iy = int((cc0 / n) % n);
-  const bool send_x = ix < n - 1 && (lane & 15) != 15, recv_x = ix > 0 && (lane & 15) != 0;
-  const bool send_y = iy < n - 1 && lane + n < 64, recv_y = iy > 0 && lane >= n;
-#pragma unroll
-  for (int z = 0; z < 3; ++z)
-#pragma unroll
-    for (int yy = 0; yy < 3; ++yy) {
-      const T r = from_left_lane(w[2 + 3 * yy + 9 * z]);
-      if (recv_x) w[3 * yy + 9 * z] += r;
-      if (send_x) w[2 + 3 * yy + 9 * z] = T(0);   // handed over
-    }
-#pragma unroll
-  for (int z = 0; z < 3; ++z)
-#pragma unroll
-    for (int xx = 0; xx < 3; ++xx) {
-      const T r = __shfl_up(w[xx + 6 + 9 * z], unsigned(n));
-      if (recv_y) w[xx + 9 * z] += r;
-    }
-  if (!live) return;
-#pragma unroll
-  for (int z = 0; z < 3; ++z)
-#pragma unroll
-    for (int yy = 0; yy < 3; ++yy)
-#pragma unroll
-      for (int xx = 0; xx < 3; ++xx) {
-        const int32_t sl = uc.slot(xx, yy, z);
-        if (sl >= 0 && !(xx == 2 && send_x) && !(yy == 2 && send_y))
-          atomic_add(&y[3 * int64_t(sl) + c], w[xx + 3 * yy + 9 * z]);
-      }
 }
 
 // y(node) += the face slots of the node (one thread per node, 2-8 slots)
@@ -223,7 +117,7 @@ double* face_slots<double>(const DevLevel& L) {
 
 // The single cells of a non-uniform level (those in no block): the cell
 // operator with three threads per cell, one velocity component each (a wave
-// per component, as k_vmult_uniform3), hanging nodes resolved through the
+// per component), hanging nodes resolved through the
 // level's constraint rows (HANG).  A thread gathers,
 // transforms and scatters its component's 27 values and computes its
 // component's rows of the cell operator from the modes of all three
@@ -648,28 +542,21 @@ __global__ void k_invert_diag_general(int64_t nn, const uint8_t* __restrict__ cm
 
 // ------------------------------------------------------------- Chebyshev
 // The smoother's Chebyshev updates (k_chebx_*) can also prepare the output of
-// the next operator call on levels whose operator otherwise starts with an
-// initialisation kernel (k_init_out_*): tn = (constrained dof ? src : 0), src
-// being the new d, or the new x when from_x.  Constrained: the dof's bit of
-// cmask on general levels (cmask given), a boundary node of the m^3 lattice on
-// uniform ones.  tn may be t itself (each entry is read before it is written, by the
-// same thread; t and tn are therefore not restrict).
+// the next operator call on general levels, whose operator otherwise starts
+// with an initialisation kernel (k_init_out_general): tn = the new x on
+// constrained dofs (their bits of cmask), 0 elsewhere.  tn may be t itself
+// (each entry is read before it is written, by the same thread; t and tn are
+// therefore not restrict).
 template <typename T>
 struct OutPrep {
   T* tn;
   const uint8_t* cmask;
-  int64_t m;
-  int from_x;
 };
-__device__ __forceinline__ bool constrained_dof(int64_t i, const uint8_t* cmask, int64_t m) {
-  const int64_t v = i / 3;
-  if (cmask) return (cmask[v] >> (i - 3 * v)) & 1;
-  const int64_t X = v % m, Y = (v / m) % m, Z = v / (m * m);
-  return X == 0 || Y == 0 || Z == 0 || X == m - 1 || Y == m - 1 || Z == m - 1;
-}
 template <typename T>
-__device__ __forceinline__ void out_prep(const OutPrep<T>& o, int64_t i, T di, T xi) {
-  if (o.tn) o.tn[i] = constrained_dof(i, o.cmask, o.m) ? (o.from_x ? xi : di) : T(0);
+__device__ __forceinline__ void out_prep(const OutPrep<T>& o, int64_t i, T xi) {
+  if (!o.tn) return;
+  const int64_t v = i / 3;
+  o.tn[i] = ((o.cmask[v] >> (i - 3 * v)) & 1) ? xi : T(0);
 }
 
 template <typename T>
@@ -730,7 +617,7 @@ __global__ void k_chebx_init0(int64_t n, const T* __restrict__ b, const T* __res
     const T di = minv[i] * b[i] * it;
     d[i] = di;
     x[i] = di;
-    out_prep(o, i, di, di);
+    out_prep(o, i, di);
   }
 }
 template <typename T>
@@ -744,7 +631,7 @@ __global__ void k_chebx_step(int64_t n, const T* __restrict__ b, const T* t, con
     const T xi = x[i] + di;
     d[i] = di;
     x[i] = xi;
-    out_prep(o, i, di, xi);
+    out_prep(o, i, xi);
   }
 }
 
@@ -1166,7 +1053,7 @@ __global__ __launch_bounds__(128) void k_coarse(const T* __restrict__ Ainv, cons
 // instead of the ~22 kernel boundaries the level takes otherwise, each of
 // which costs more than the level's arithmetic.  Every step computes what its
 // kernel computes (some sums in another order): the Chebyshev
-// updates of k_chebx_init0 / k_chebx_step, the operator of k_vmult_uniform3
+// updates of k_chebx_init0 / k_chebx_step, the cell operator
 // (three threads per cell; its sums go into LDS), the passes of
 // k_restrict_x_rows / k_restrict_y / k_restrict_z, k_coarse (a row's sum in
 // three parts) and the prolongation (here by axes, z, y, x).  Pre-smoothing
@@ -2338,8 +2225,9 @@ double* brick_halo<double>(const DevLevel& L) {
 template <typename T>
 bool brick_fits(int64_t n) {
   // below 32 cells per edge there are too few bricks to fill the chip and a
-  // brick's latency dominates: the cell-parallel kernel is faster there
-  return n % 8 == 0 && n <= 256 && n >= kBrickMinEdge;
+  // brick's latency dominates; at 32^3 the owner kernel is the faster one in
+  // FP32 (12.3 against 14.3 us) and the slower one in FP64 (19.5 against 17.3)
+  return n % 8 == 0 && n <= 256 && n >= (sizeof(T) == 4 ? 64 : 32);
 }
 
 template <typename T>
@@ -2366,6 +2254,22 @@ void launch_brick(const DevLevel& L, const T* x, T* y, T* halo, bool init, hipSt
       <<<unsigned(nb * brick::HaloClasses<BX, BY, BZ>::groups), 256, 0, s>>>(int(n), !init, halo, y);
 }
 
+// 2 x 2 x 2 bricks up to 16^3 cells, 4 x 2 x 2 beyond (both measured, see
+// owner_kernel.h)
+template <owner::Op OP, typename T>
+void launch_owner(const DevLevel& L, const T* x, const T* b, const T* minv, T* d, T* y, double alpha, double beta,
+                  double it0, hipStream_t s) {
+  const int64_t n = L.n_edge;
+  const owner::Args<T> a{int(n), mu_of<T>(L), x, b, minv, d, y, T(alpha), T(beta), T(it0)};
+  if (n <= 16) {
+    owner::k_owner<T, 1, int, OP><<<unsigned(n * n * n / 8), owner::kThreads, 0, s>>>(a);
+  } else if (n <= kFusedMaxEdge) {
+    owner::k_owner<T, 2, int, OP><<<unsigned(n * n * n / 16), owner::kThreads, 0, s>>>(a);
+  } else if constexpr (OP == owner::Op::Apply || OP == owner::Op::Add) {   // beyond the brick kernel's index range
+    owner::k_owner<T, 2, int64_t, OP><<<unsigned(n * n * n / 16), owner::kThreads, 0, s>>>(a);
+  }
+}
+
 template <typename T>
 void vmult_impl(const DevLevel& L, const T* x, T* y, hipStream_t s, bool init, bool prepared) {
   if (L.uniform) {
@@ -2374,9 +2278,10 @@ void vmult_impl(const DevLevel& L, const T* x, T* y, hipStream_t s, bool init, b
     if (halo && brick_fits<T>(n)) {
       if (brick::brick_by(n) == 8) launch_brick<T, 8, 8, 4>(L, x, y, halo, init, s);
       else launch_brick<T, 8, 4, 4>(L, x, y, halo, init, s);
+    } else if (init) {
+      launch_owner<owner::Op::Apply, T>(L, x, nullptr, nullptr, nullptr, y, 0.0, 0.0, 0.0, s);
     } else {
-      if (init && !prepared) k_init_out_uniform<T><<<grid_for(L.nnode), kBlock, 0, s>>>(L.n_edge, x, y);
-      k_vmult_uniform3<T><<<unsigned((L.ncell + 63) / 64), 192, 0, s>>>(n, mu_of<T>(L), x, y);
+      launch_owner<owner::Op::Add, T>(L, x, nullptr, nullptr, nullptr, y, 0.0, 0.0, 0.0, s);
     }
     return;
   }
@@ -2415,14 +2320,36 @@ template <typename T>
 void launch_vmult_prepared(const DevLevel& L, const T* x, T* y, hipStream_t s) {
   vmult_impl<T>(L, x, y, s, true, true);
 }
+bool vmult_has_init(const DevLevel& L) { return !L.q3 && !L.uniform; }
+
+bool smoother_fuses(const DevLevel& L) { return L.uniform && L.n_edge <= kFusedMaxEdge; }
 template <typename T>
-bool vmult_has_init(const DevLevel& L) {
-  return !L.q3 && !(L.uniform && brick_halo<T>(L) && brick_fits<T>(L.n_edge));
+void launch_fused_first(const DevLevel& L, const T* b, const T* minv, T* d, T* y, double it0, double alpha,
+                        double beta, hipStream_t s) {
+  launch_owner<owner::Op::First, T>(L, nullptr, b, minv, d, y, alpha, beta, it0, s);
 }
+template <typename T>
+void launch_fused_step(const DevLevel& L, const T* x, const T* b, const T* minv, T* d, T* y, double alpha, double beta,
+                       bool last, hipStream_t s) {
+  if (alpha == 0.0) launch_owner<owner::Op::Start, T>(L, x, b, minv, d, y, alpha, beta, 0.0, s);
+  else if (last) launch_owner<owner::Op::Last, T>(L, x, b, minv, d, y, alpha, beta, 0.0, s);
+  else launch_owner<owner::Op::Step, T>(L, x, b, minv, d, y, alpha, beta, 0.0, s);
+}
+template <typename T>
+void launch_fused_residual(const DevLevel& L, const T* x, const T* b, T* y, hipStream_t s) {
+  launch_owner<owner::Op::Residual, T>(L, x, b, nullptr, nullptr, y, 0.0, 0.0, 0.0, s);
+}
+#define MFGMG_FUSED(T)                                                                                              \
+  template void launch_fused_first<T>(const DevLevel&, const T*, const T*, T*, T*, double, double, double,          \
+                                      hipStream_t);                                                                 \
+  template void launch_fused_step<T>(const DevLevel&, const T*, const T*, const T*, T*, T*, double, double, bool,   \
+                                     hipStream_t);                                                                  \
+  template void launch_fused_residual<T>(const DevLevel&, const T*, const T*, T*, hipStream_t);
+MFGMG_FUSED(float)
+MFGMG_FUSED(double)
+#undef MFGMG_FUSED
 template void launch_vmult_prepared<float>(const DevLevel&, const float*, float*, hipStream_t);
 template void launch_vmult_prepared<double>(const DevLevel&, const double*, double*, hipStream_t);
-template bool vmult_has_init<float>(const DevLevel&);
-template bool vmult_has_init<double>(const DevLevel&);
 template void launch_vmult<float>(const DevLevel&, const float*, float*, hipStream_t, bool);
 template void launch_vmult<double>(const DevLevel&, const double*, double*, hipStream_t, bool);
 
@@ -2451,11 +2378,6 @@ void launch_invert_diag(const DevLevel& L, const double* d, double* md, float* m
 }
 
 template <typename T>
-OutPrep<T> out_prep_of(const ChebPrep& p) {
-  OutPrep<T> o{static_cast<T*>(p.tn), p.cmask, p.m, p.from_x ? 1 : 0};
-  return o;
-}
-template <typename T>
 void launch_cheb_init0(int64_t n, const T* b, const T* minv, T* r, T* d, T* x, double it, hipStream_t s) {
   k_cheb_init0<T><<<grid_for(n), kBlock, 0, s>>>(n, b, minv, r, d, x, T(it));
 }
@@ -2471,12 +2393,13 @@ void launch_cheb_step(int64_t n, const T* t, const T* minv, T* r, T* d, T* x, do
 template <typename T>
 void launch_chebx_init0(int64_t n, const T* b, const T* minv, T* d, T* x, double it, hipStream_t s,
                         const ChebPrep& p) {
-  k_chebx_init0<T><<<grid_for(n), kBlock, 0, s>>>(n, b, minv, d, x, T(it), out_prep_of<T>(p));
+  k_chebx_init0<T><<<grid_for(n), kBlock, 0, s>>>(n, b, minv, d, x, T(it), OutPrep<T>{static_cast<T*>(p.tn), p.cmask});
 }
 template <typename T>
 void launch_chebx_step(int64_t n, const T* b, const T* t, const T* minv, T* d, T* x, double alpha, double beta,
                        hipStream_t s, const ChebPrep& p) {
-  k_chebx_step<T><<<grid_for(n), kBlock, 0, s>>>(n, b, t, minv, d, x, T(alpha), T(beta), out_prep_of<T>(p));
+  k_chebx_step<T><<<grid_for(n), kBlock, 0, s>>>(n, b, t, minv, d, x, T(alpha), T(beta),
+                                               OutPrep<T>{static_cast<T*>(p.tn), p.cmask});
 }
 template void launch_chebx_init0<float>(int64_t, const float*, const float*, float*, float*, double, hipStream_t,
                                         const ChebPrep&);
