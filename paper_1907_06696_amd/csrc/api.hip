@@ -846,15 +846,30 @@ const double* ainv_of<double>(mfgmg_ctx* ctx) {
 }
 
 template <typename T>
+const T* tail_of(mfgmg_ctx* ctx);
+template <>
+const float* tail_of<float>(mfgmg_ctx* ctx) {
+  return ctx->tail_f;
+}
+template <>
+const double* tail_of<double>(mfgmg_ctx* ctx) {
+  return ctx->tail_d;
+}
+
+template <typename T>
 void vcycle(mfgmg_ctx* ctx, int ell, const T* b, T* x, hipStream_t s) {
   if (ell == 1) {
-    launch_coarse<T>(ainv_of<T>(ctx), ctx->coarse_free, ctx->ncfree, int(3 * ctx->lv[1].v.nnode), b, x, s);
+    launch_dense<T>(ainv_of<T>(ctx), ctx->coarse_free, ctx->ncfree, int(3 * ctx->lv[1].v.nnode), 1.0, b, x, s);
     return;
   }
   LevelDev& d = ctx->lv[size_t(ell)];
   LevelDev& c = ctx->lv[size_t(ell - 1)];
-  if (ell == 2) {   // the 4^3 level and the coarse solve in one workgroup, where it applies
+  if (ell == 2) {   // the 4^3 level and the coarse solve in one kernel, where it applies
     const bool sc = ctx->use_scaling && d.scaled;
+    if (tail_of<T>(ctx) && !sc) {
+      launch_dense<T>(tail_of<T>(ctx), ctx->tail.free, ctx->tail.nfree, int(3 * d.v.nnode), ctx->tail_c, b, x, s);
+      return;
+    }
     if (launch_vcycle_tail<T>(d.v, c.v, sc ? minv_s_of<T>(d) : minv_of<T>(d), ainv_of<T>(ctx), ctx->coarse_free,
                               ctx->ncfree, sc ? d.lambda_s : d.lambda, b, x, s))
       return;
@@ -992,6 +1007,54 @@ int factor_coarse(mfgmg_ctx* ctx, hipStream_t s) {
   std::vector<float> Aff(Af.begin(), Af.end());
   HIPCHK(hipMemcpyAsync(ctx->Ainv_d, Af.data(), Af.size() * sizeof(double), hipMemcpyHostToDevice, s));
   HIPCHK(hipMemcpyAsync(ctx->Ainv_f, Aff.data(), Aff.size() * sizeof(float), hipMemcpyHostToDevice, s));
+  HIPCHK(hipStreamSynchronize(s));
+  return MFGMG_OK;
+}
+
+// The 4^3 level's V-cycle as a dense matrix (after factor_coarse and the
+// level's eigenvalue estimate), where level 2 is a full 4^3 Q2 level
+int build_tail(mfgmg_ctx* ctx, hipStream_t s) {
+  const Mesh& m = *ctx->mesh;
+  if (m.velocity_degree() != 2 || m.L() < 2 || m.level(2).ncell != 64) return MFGMG_OK;
+  const Level &h = m.level(2), &c = m.level(1);
+  if (!ctx->tail_d) {
+    const int64_t S1 = m.S() + 1;
+    auto lattice = [&](const Level& lv, int64_t i) {   // lattice node of storage node i
+      const int64_t step = m.S() / (2 << lv.ell), mm = (4 << (lv.ell - 1)) + 1, k = lv.key[size_t(i)];
+      return int32_t(k % S1 / step + mm * (k / S1 % S1 / step + mm * (k / (S1 * S1) / step)));
+    };
+    std::vector<int32_t> node(static_cast<size_t>(h.nnode)), lat(static_cast<size_t>(h.nnode));
+    std::vector<int32_t> clat(static_cast<size_t>(c.nnode)), cell(64), fd;
+    for (int64_t i = 0; i < h.nnode; ++i) {
+      lat[size_t(i)] = lattice(h, i);
+      node[size_t(lat[size_t(i)])] = int32_t(i);
+      for (int q = 0; q < 3; ++q)
+        if (h.dof_free(i, q)) fd.push_back(int32_t(3 * i + q));
+    }
+    for (int64_t i = 0; i < c.nnode; ++i) clat[size_t(i)] = lattice(c, i);
+    for (int i = 0; i < 64; ++i)
+      cell[size_t(h.cijk[size_t(3 * i)] + 4 * (h.cijk[size_t(3 * i + 1)] + 4 * h.cijk[size_t(3 * i + 2)]))] = i;
+    const size_t nf = fd.size();
+    ctx->tail.node = ctx->upload(node);
+    ctx->tail.lattice = ctx->upload(lat);
+    ctx->tail.coarse_lattice = ctx->upload(clat);
+    ctx->tail.cell = ctx->upload(cell);
+    ctx->tail.free = ctx->upload(fd);
+    ctx->tail.nfree = int(nf);
+    double* Vd = ctx->dalloc<double>(nf * nf);
+    ctx->tail_f = ctx->dalloc<float>(nf * nf);
+    if (!ctx->tail.node || !ctx->tail.lattice || !ctx->tail.coarse_lattice || !ctx->tail.cell || !ctx->tail.free ||
+        !Vd || !ctx->tail_f) {
+      ctx->tail_f = nullptr;
+      return ctx->set(MFGMG_ERR_NOMEM, "device allocation failed");
+    }
+    ctx->tail_d = Vd;
+  }
+  const LevelDev& d = ctx->lv[2];
+  ctx->tail_c = launch_tail_columns(ctx->tail, m.noflux(), d.mu_d, d.minv_d, ctx->Ainv_d, ctx->coarse_free, d.lambda,
+                                    ctx->tail_d, s);
+  launch_to_float(int64_t(ctx->tail.nfree) * ctx->tail.nfree, ctx->tail_d, ctx->tail_f, s);
+  HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(s));
   return MFGMG_OK;
 }
@@ -1303,6 +1366,8 @@ int mfgmg_set_viscosity(mfgmg_ctx* ctx, const double* mu_qp, void* stream) {
     if (st) return st;
   }
   st = factor_coarse(ctx, s);
+  if (st) return st;
+  st = build_tail(ctx, s);
   if (st) return st;
   st = pressure_setup(ctx, s);
   if (st) return st;

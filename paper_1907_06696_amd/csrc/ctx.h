@@ -66,6 +66,12 @@ struct mfgmg_ctx {
   float* Ainv_f = nullptr;
   int32_t* coarse_free = nullptr;
   int ncfree = 0;
+  // V-cycle of a full 4^3 level as a dense matrix over its free dofs (null
+  // where level 2 is not one), and its factor on the constrained dofs
+  mfgmg::TailMaps tail;
+  double* tail_d = nullptr;
+  float* tail_f = nullptr;
+  double tail_c = 0.0;
   double* red_part = nullptr;   // reduction partials
   double* red_res = nullptr;    // device results (up to 128)
   double* host_res = nullptr;   // pinned host copy

@@ -226,11 +226,28 @@ template <typename T>
 void launch_restrict_level(const DevLevel& fine, const DevLevel& coarse, const int64_t* ptr, const int32_t* col,
                            const float* w, const T* b, const T* t, T* xc, T* s1, T* s2, hipStream_t s);
 
-// coarse solve: x[free] = Ainv b[free], x[constrained] = b
+// x[free] = A b[free] with a dense A [nfree][nfree] over the free dofs fd
+// (increasing), x = cfac b on the other entries of the n; x must not be b.
+// The coarse solve (A its inverse, cfac 1) and the 4^3 level's V-cycle.
 template <typename T>
-void launch_coarse(const T* Ainv, const int32_t* free_dofs, int nfree, int n, const T* b, T* x, hipStream_t s);
+void launch_dense(const T* A, const int32_t* fd, int nfree, int n, double cfac, const T* b, T* x, hipStream_t s);
+// Node and cell orders of a full 4^3 level and the 2^3 level below it: storage
+// node of each lattice node and back, lattice node of each coarse storage
+// node, storage cell of each lattice cell, free dofs (storage order)
+struct TailMaps {
+  const int32_t* node = nullptr;
+  const int32_t* lattice = nullptr;
+  const int32_t* coarse_lattice = nullptr;
+  const int32_t* cell = nullptr;
+  const int32_t* free = nullptr;
+  int nfree = 0;
+};
+// The 4^3 level's V-cycle (coarse solve included) as a dense matrix V
+// [nfree][nfree] over its free dofs; returns its factor on the constrained ones.
+double launch_tail_columns(const TailMaps& tm, bool noflux, const double* mu, const double* minv, const double* Ainv,
+                           const int32_t* fd, double lam, double* V, hipStream_t s);
 // One V-cycle on the uniform 4^3 level L with the coarse solve of the 2^3
-// level Lc below it (Ainv, free_dofs, nfree as for launch_coarse), smoother
+// level Lc below it (Ainv, free_dofs, nfree as for launch_dense), smoother
 // M^-1 = minv on [lam / 15, lam], in a single workgroup; the same steps as
 // smoothing, residual, restriction, coarse solve, prolongation and smoothing
 // launched one by one.  Returns false (nothing launched) when L, Lc are not

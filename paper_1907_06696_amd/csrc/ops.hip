@@ -746,12 +746,13 @@ __global__ __launch_bounds__(kBlock) void k_restrict(int64_t nc, const int64_t* 
 // the exact transpose: coarse node C collects fine X = 2C (weight 1) and, for
 // even C, 2C+-1 (3/8) and 2C+-3 (-1/8); for odd C, 2C+-1 (3/4).  Boundary
 // (Dirichlet) nodes of either level carry and receive nothing.
+// (open: nodes on the axis' two boundary planes take part)
 template <typename T>
-__device__ __forceinline__ int prolong_axis(int X, int mc, int (&idx)[3], T (&w)[3]) {
+__device__ __forceinline__ int prolong_axis(int X, int mc, int (&idx)[3], T (&w)[3], bool open = false) {
   if (!(X & 1)) {
     const int c = X >> 1;
     idx[0] = c, w[0] = T(1);
-    return (c == 0 || c == mc - 1) ? 0 : 1;
+    return (c == 0 || c == mc - 1) && !open ? 0 : 1;
   }
   const int base = 2 * (X >> 2);
   const bool q1 = (X & 3) == 1;
@@ -759,8 +760,8 @@ __device__ __forceinline__ int prolong_axis(int X, int mc, int (&idx)[3], T (&w)
   w[0] = q1 ? T(0.375) : T(-0.125);
   w[1] = T(0.75);
   w[2] = q1 ? T(-0.125) : T(0.375);
-  if (base == 0) w[0] = T(0);
-  if (base + 2 == mc - 1) w[2] = T(0);
+  if (base == 0 && !open) w[0] = T(0);
+  if (base + 2 == mc - 1 && !open) w[2] = T(0);
   return 3;
 }
 
@@ -1028,21 +1029,43 @@ __global__ __launch_bounds__(kBlock) void k_restrict_z(int nc, const T* __restri
 }
 
 // ------------------------------------------------------------- coarse
-// the level-1 mesh (2^3 cells) has 125 Q2 nodes: at most 375 free dofs (81
-// under u = 0, 225 under u . n = 0)
-constexpr int kCoarseMaxFree = 375;
-template <typename T>
-__global__ __launch_bounds__(128) void k_coarse(const T* __restrict__ Ainv, const int32_t* __restrict__ fd,
-                                                int nfree, int n, const T* __restrict__ b, T* __restrict__ x) {
-  __shared__ T bs[kCoarseMaxFree];
-  for (int i = threadIdx.x; i < nfree; i += blockDim.x) bs[i] = b[fd[i]];
-  for (int i = threadIdx.x; i < n; i += blockDim.x) x[i] = b[i];
-  __syncthreads();
-  for (int r = threadIdx.x; r < nfree; r += blockDim.x) {
-    T acc = T(0);
-    for (int j = 0; j < nfree; ++j) acc += Ainv[r * nfree + j] * bs[j];
-    x[fd[r]] = acc;
+// The level-1 mesh (2^3 cells) has 81 free dofs under u = 0, 225 under u . n =
+// 0 and 375 with the Q3 element.
+// x[free] = A b[free] with a dense A, x = cfac b on the other dofs: one wave
+// per row (its NK words per lane loaded before b is waited for), four rows a
+// workgroup, and a last workgroup for the other dofs.  A single workgroup
+// with a thread per row took 23 us for 225 rows and 58 us for 375, a serial
+// chain of strided loads; this takes 3-5 us.
+constexpr int kDenseMax = 27 * 64;     // rows: the 4^3 level under u . n = 0 has 1701
+constexpr int kDenseDofs = 3 * 729;    // entries, free or not
+template <typename T, int NK>
+__global__ __launch_bounds__(256) void k_dense(const T* __restrict__ A, const int32_t* __restrict__ fd, int nfree,
+                                               int n, T cfac, const T* __restrict__ b, T* __restrict__ x) {
+  __shared__ T bs[64 * NK];
+  __shared__ uint8_t is_free[kDenseDofs];
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (blockIdx.x == gridDim.x - 1) {
+    for (int i = tid; i < n; i += 256) is_free[i] = 0;
+    __syncthreads();
+    for (int r = tid; r < nfree; r += 256) is_free[fd[r]] = 1;
+    __syncthreads();
+    for (int i = tid; i < n; i += 256)
+      if (!is_free[i]) x[i] = cfac * b[i];
+    return;
   }
+  const int row = 4 * int(blockIdx.x) + __builtin_amdgcn_readfirstlane(tid >> 6);
+  const T* Ar = A + int64_t(min(row, nfree - 1)) * nfree;
+  T v[NK];
+#pragma unroll
+  for (int k = 0; k < NK; ++k) v[k] = Ar[min(lane + 64 * k, nfree - 1)];
+  for (int i = tid; i < 64 * NK; i += 256) bs[i] = i < nfree ? b[fd[i]] : T(0);
+  __syncthreads();
+  T acc = T(0);
+#pragma unroll
+  for (int k = 0; k < NK; ++k) acc += v[k] * bs[lane + 64 * k];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+  if (lane == 0 && row < nfree) x[fd[row]] = acc;
 }
 
 // ------------------------------------------------------------- the 4^3 level
@@ -1055,7 +1078,7 @@ __global__ __launch_bounds__(128) void k_coarse(const T* __restrict__ Ainv, cons
 // kernel computes (some sums in another order): the Chebyshev
 // updates of k_chebx_init0 / k_chebx_step, the cell operator
 // (three threads per cell; its sums go into LDS), the passes of
-// k_restrict_x_rows / k_restrict_y / k_restrict_z, k_coarse (a row's sum in
+// k_restrict_x_rows / k_restrict_y / k_restrict_z, the coarse solve (a row's sum in
 // three parts) and the prolongation (here by axes, z, y, x).  Pre-smoothing
 // starts from x = 0; post-smoothing's first step has alpha = 0; steps 1-3 of
 // both take (alpha_k, beta_k).
@@ -1063,16 +1086,28 @@ template <typename T>
 struct TailCoef {
   T it0, alpha[4], beta[4];
 };
-constexpr int kTailN = 4, kTailFree = 81;   // free dofs of the 2^3 level under u = 0
-template <typename T>
+//
+// The cycle is a fixed linear map of the level's free dofs, so once the
+// viscosity is set it is kept as a dense matrix (1,029^2 under u = 0, 1,701^2
+// under u . n = 0) and applied by k_dense in ~5 us, where this kernel takes 45
+// to 60 us (about 60 barriers in one workgroup; separate kernels 220 us under
+// u . n = 0).  COLS builds that matrix: workgroup j runs the cycle on the unit
+// vector of free dof j and stores the result as column j (one launch).  The
+// plain form runs the cycle where the smoother carries an installed scaling,
+// which changes with every fit.  NOFLUX (only with COLS): component c is
+// fixed on the faces normal to axis c alone, and nodes and cells are
+// stored in the order of the maps.
+constexpr int kTailN = 4, kTailFree = 81;   // free dofs of the 2^3 level under u = 0 (225 under u . n = 0)
+template <typename T, bool COLS, bool NOFLUX>
 __global__ __launch_bounds__(256) void k_vcycle_tail(const T* __restrict__ mu, const T* __restrict__ minv,
                                                      const T* __restrict__ Ainv, const int32_t* __restrict__ fd,
-                                                     TailCoef<T> cf, const T* __restrict__ b, T* __restrict__ x) {
+                                                     TailCoef<T> cf, const T* __restrict__ b, T* __restrict__ x,
+                                                     TailMaps tm) {
   constexpr int n = kTailN, m = 2 * n + 1, NV = 3 * m * m * m, KV = (NV + 255) / 256;
   constexpr int mc = n + 1, mf = m, NC = 3 * mc * mc * mc;
   __shared__ T xs[NV], ts[NV], bs[NV], ds[NV], ms[NV];
   __shared__ T wsh[3][27][64];
-  __shared__ T s1[3 * mc * mf * mf], s2[3 * mc * mc * mf], bc[NC], xc[NC], bf[kTailFree], part[3 * kTailFree];
+  __shared__ T s1[3 * mc * mf * mf], s2[3 * mc * mc * mf], bc[NC], xc[NC], bf[3 * kTailFree], part[3 * kTailFree];
   const int tid = threadIdx.x;
   // this thread's entries tid + 256 k: in range (bit k of `live`) and on a
   // boundary node (`fixed`).  Wherever x changes, ts is set to x on the
@@ -1083,19 +1118,41 @@ __global__ __launch_bounds__(256) void k_vcycle_tail(const T* __restrict__ mu, c
   for (int k = 0; k < KV; ++k) {
     const int i = tid + 256 * k, v = i / 3, X = v % m, Y = (v / m) % m, Z = v / (m * m);
     if (i < NV) live |= 1u << k;
-    if (i < NV && (X == 0 || Y == 0 || Z == 0 || X == m - 1 || Y == m - 1 || Z == m - 1)) fixed |= 1u << k;
+    bool fx = X == 0 || Y == 0 || Z == 0 || X == m - 1 || Y == m - 1 || Z == m - 1;
+    if constexpr (NOFLUX) {
+      const int W = i % 3 == 0 ? X : i % 3 == 1 ? Y : Z;
+      fx = W == 0 || W == m - 1;
+    }
+    if (i < NV && fx) fixed |= 1u << k;
   }
+  // storage index of lattice entry i of this level, and the coarse lattice
+  // entry of coarse storage entry i
+  auto stored = [&](int i) { return COLS ? 3 * tm.node[i / 3] + i % 3 : i; };
+  auto coarse_entry = [&](int i) { return COLS ? 3 * tm.coarse_lattice[i / 3] + i % 3 : i; };
   auto each = [&](auto f) {
 #pragma unroll
     for (int k = 0; k < KV; ++k)
       if ((live >> k) & 1) f(tid + 256 * k, ((fixed >> k) & 1) != 0);
   };
-  each([&](int i, bool) { bs[i] = b[i], ms[i] = minv[i]; });
+  if constexpr (COLS) {
+    const int unit = tm.free[blockIdx.x];
+    each([&](int i, bool) { bs[i] = T(stored(i) == unit ? 1 : 0), ms[i] = minv[stored(i)]; });
+  } else {
+    each([&](int i, bool) { bs[i] = b[i], ms[i] = minv[i]; });
+  }
   // the operator's thread: cell `cell`, output component c (waves 0-2)
   const bool opt = tid < 192;
   const int c = tid >> 6, cell = tid & 63;
   const UniformCell uc(n, cell);
-  const T mu_h = opt ? mu[cell] / T(n) : T(0);
+  const T mu_h = opt ? mu[COLS ? tm.cell[cell] : cell] / T(n) : T(0);
+  // lattice node of a local node of this thread's cell, -1 where its
+  // component is fixed
+  auto slot = [&](int xx, int yy, int zz) {
+    if constexpr (!NOFLUX) return uc.slot(xx, yy, zz);
+    const int w = c == 0 ? xx : c == 1 ? yy : zz;
+    const bool fx = (w == 0 && uc.lo[c]) || (w == 2 && uc.hi[c]);
+    return fx ? -1 : int32_t(uc.base + xx + m * (yy + m * zz));
+  };
   __syncthreads();
   auto apply = [&]() {   // ts += the cells' sums: ts = A xs
     T w[27];
@@ -1106,7 +1163,7 @@ __global__ __launch_bounds__(256) void k_vcycle_tail(const T* __restrict__ mu, c
         for (int yy = 0; yy < 3; ++yy)
 #pragma unroll
           for (int xx = 0; xx < 3; ++xx) {
-            const int32_t sl = uc.slot(xx, yy, z);
+            const int32_t sl = slot(xx, yy, z);
             const T v = xs[3 * max(sl, 0) + c];   // every read issued, the Dirichlet ones dropped
             w[xx + 3 * yy + 9 * z] = sl >= 0 ? v : T(0);
           }
@@ -1129,7 +1186,7 @@ __global__ __launch_bounds__(256) void k_vcycle_tail(const T* __restrict__ mu, c
           for (int yy = 0; yy < 3; ++yy)
 #pragma unroll
             for (int xx = 0; xx < 3; ++xx) {
-              const int32_t sl = uc.slot(xx, yy, z);
+              const int32_t sl = slot(xx, yy, z);
               if (sl >= 0) atomicAdd(&ts[3 * sl + c], w[xx + 3 * yy + 9 * z]);
             }
       } else {
@@ -1150,14 +1207,14 @@ __global__ __launch_bounds__(256) void k_vcycle_tail(const T* __restrict__ mu, c
             for (int yy = b0; yy < b1; ++yy)
 #pragma unroll
               for (int xx = a0; xx < a1; ++xx)
-                old[(xx - a0) + 2 * (yy - b0) + 4 * (z - z0)] = ts[3 * max(uc.slot(xx, yy, z), 0) + c];
+                old[(xx - a0) + 2 * (yy - b0) + 4 * (z - z0)] = ts[3 * max(slot(xx, yy, z), 0) + c];
 #pragma unroll
           for (int z = z0; z < z1; ++z)
 #pragma unroll
             for (int yy = b0; yy < b1; ++yy)
 #pragma unroll
               for (int xx = a0; xx < a1; ++xx) {
-                const int32_t sl = uc.slot(xx, yy, z);
+                const int32_t sl = slot(xx, yy, z);
                 if (sl >= 0) ts[3 * sl + c] = old[(xx - a0) + 2 * (yy - b0) + 4 * (z - z0)] + w[xx + 3 * yy + 9 * z];
               }
           wave_lds_sync();
@@ -1183,11 +1240,15 @@ __global__ __launch_bounds__(256) void k_vcycle_tail(const T* __restrict__ mu, c
     for (int v = tid; v < 3 * mc * mf * mf; v += 256) {
       const int comp = v % 3, o = v / 3, cx = o % mc, fy = (o / mc) % mf, fz = o / (mc * mf);
       T a = T(0);
-      if (fy > 0 && fy < mf - 1 && fz > 0 && fz < mf - 1) {
+      // fixed entries of the residual count 0
+      auto inside = [&](int w, int axis) {
+        return (NOFLUX && comp != axis) ? w >= 0 && w < mf : w > 0 && w < mf - 1;
+      };
+      if (inside(fy, 1) && inside(fz, 2)) {
 #pragma unroll
         for (int qq = 0; qq < 5; ++qq) {
           const int fx = 2 * cx + restrict_off(qq);
-          if (fx > 0 && fx < mf - 1) {
+          if (inside(fx, 0)) {
             const int f = 3 * (fx + mf * (fy + mf * fz)) + comp;
             a += restrict_w<T>(cx, qq) * (bs[f] - ts[f]);
           }
@@ -1210,7 +1271,8 @@ __global__ __launch_bounds__(256) void k_vcycle_tail(const T* __restrict__ mu, c
     for (int v = tid; v < NC; v += 256) {
       const int comp = v % 3, o = v / 3, cx = o % mc, cy = (o / mc) % mc, cz = o / (mc * mc);
       T a = T(0);
-      if (cx > 0 && cx < mc - 1 && cy > 0 && cy < mc - 1 && cz > 0 && cz < mc - 1) {
+      auto inside = [&](int w, int axis) { return (NOFLUX && comp != axis) || (w > 0 && w < mc - 1); };
+      if (inside(cx, 0) && inside(cy, 1) && inside(cz, 2)) {
 #pragma unroll
         for (int qq = 0; qq < 5; ++qq) {
           const int fz = 2 * cz + restrict_off(qq);
@@ -1223,10 +1285,17 @@ __global__ __launch_bounds__(256) void k_vcycle_tail(const T* __restrict__ mu, c
     // coarse solve on the free dofs (the others keep b): three threads per
     // row of Ainv, each summing a third of its columns (all loads issued
     // first), then the row's first thread adds the three sums
-    for (int i = tid; i < kTailFree; i += 256) bf[i] = bc[fd[i]];
+    constexpr int kFree = NOFLUX ? 225 : kTailFree;
+    for (int i = tid; i < kFree; i += 256) bf[i] = bc[coarse_entry(fd[i])];
     for (int i = tid; i < NC; i += 256) xc[i] = bc[i];
     __syncthreads();
-    {
+    if constexpr (NOFLUX) {   // one thread per row
+      if (tid < kFree) {
+        T a = T(0);
+        for (int j = 0; j < kFree; ++j) a += Ainv[tid * kFree + j] * bf[j];
+        xc[coarse_entry(fd[tid])] = a;
+      }
+    } else {
       constexpr int JC = kTailFree / 3;
       const int r = tid % kTailFree, q = tid / kTailFree;
       if (tid < 3 * kTailFree) {
@@ -1239,7 +1308,8 @@ __global__ __launch_bounds__(256) void k_vcycle_tail(const T* __restrict__ mu, c
         part[q * kTailFree + r] = a;
       }
       __syncthreads();
-      if (tid < kTailFree) xc[fd[tid]] = (part[tid] + part[kTailFree + tid]) + part[2 * kTailFree + tid];
+      if (tid < kTailFree)
+        xc[coarse_entry(fd[tid])] = (part[tid] + part[kTailFree + tid]) + part[2 * kTailFree + tid];
     }
     __syncthreads();
     // x += P xc by axes: z (into s2 [Z][cy][cx]), y (into s1 [Z][Y][cx]), then
@@ -1249,7 +1319,7 @@ __global__ __launch_bounds__(256) void k_vcycle_tail(const T* __restrict__ mu, c
       const int comp = v % 3, o = v / 3, cx = o % mc, cy = (o / mc) % mc, Z = o / (mc * mc);
       int id[3];
       T wt[3];
-      const int nz = prolong_axis<T>(Z, mc, id, wt);
+      const int nz = prolong_axis<T>(Z, mc, id, wt, NOFLUX && comp != 2);
       T a = T(0);
       for (int k = 0; k < nz; ++k) a += wt[k] * xc[3 * (cx + mc * (cy + mc * id[k])) + comp];
       s2[v] = a;
@@ -1259,7 +1329,7 @@ __global__ __launch_bounds__(256) void k_vcycle_tail(const T* __restrict__ mu, c
       const int comp = v % 3, o = v / 3, cx = o % mc, Y = (o / mc) % mf, Z = o / (mc * mf);
       int id[3];
       T wt[3];
-      const int ny = prolong_axis<T>(Y, mc, id, wt);
+      const int ny = prolong_axis<T>(Y, mc, id, wt, NOFLUX && comp != 1);
       T a = T(0);
       for (int j = 0; j < ny; ++j) a += wt[j] * s2[3 * (cx + mc * (id[j] + mc * Z)) + comp];
       s1[v] = a;
@@ -1270,7 +1340,7 @@ __global__ __launch_bounds__(256) void k_vcycle_tail(const T* __restrict__ mu, c
         const int comp = i % 3, v = i / 3, X = v % m, YZ = v / m;
         int id[3];
         T wt[3];
-        const int nx = prolong_axis<T>(X, mc, id, wt);
+        const int nx = prolong_axis<T>(X, mc, id, wt, NOFLUX && comp != 0);
         T a = T(0);
         for (int l = 0; l < nx; ++l) a += wt[l] * s1[3 * (id[l] + mc * YZ) + comp];
         xs[i] = xs[i] + a;
@@ -1304,7 +1374,14 @@ __global__ __launch_bounds__(256) void k_vcycle_tail(const T* __restrict__ mu, c
            k == 1 ? cf.beta[1] : k == 2 ? cf.beta[2] : cf.beta[3]);
     }
   }
-  each([&](int i, bool) { x[i] = xs[i]; });
+  if constexpr (COLS) {
+    for (int r = tid; r < tm.nfree; r += 256) {
+      const int s = tm.free[r];
+      x[int64_t(r) * tm.nfree + blockIdx.x] = xs[3 * tm.lattice[s / 3] + s % 3];
+    }
+  } else {
+    each([&](int i, bool) { x[i] = xs[i]; });
+  }
 }
 
 // ------------------------------------------------------------- viscosity
@@ -2437,18 +2514,22 @@ template void launch_restrict<double>(int64_t, const int64_t*, const int32_t*, c
                                       const double*, double*, hipStream_t, const uint8_t*, const uint8_t*);
 
 template <typename T>
-void launch_coarse(const T* Ainv, const int32_t* fd, int nfree, int n, const T* b, T* x, hipStream_t s) {
-  if (nfree > kCoarseMaxFree) return;   // cannot happen: the caller checks the coarse mesh
-  k_coarse<T><<<1, 128, 0, s>>>(Ainv, fd, nfree, n, b, x);
+void launch_dense(const T* A, const int32_t* fd, int nfree, int n, double cfac, const T* b, T* x, hipStream_t s) {
+  if (nfree > kDenseMax || n > kDenseDofs) return;   // cannot happen: the caller checks the mesh
+  const unsigned g = unsigned((nfree + 3) / 4 + 1);
+  if (nfree <= 2 * 64) k_dense<T, 2><<<g, 256, 0, s>>>(A, fd, nfree, n, T(cfac), b, x);
+  else if (nfree <= 6 * 64) k_dense<T, 6><<<g, 256, 0, s>>>(A, fd, nfree, n, T(cfac), b, x);
+  else if (nfree <= 17 * 64) k_dense<T, 17><<<g, 256, 0, s>>>(A, fd, nfree, n, T(cfac), b, x);
+  else k_dense<T, 27><<<g, 256, 0, s>>>(A, fd, nfree, n, T(cfac), b, x);
 }
-template void launch_coarse<float>(const float*, const int32_t*, int, int, const float*, float*, hipStream_t);
+template void launch_dense<float>(const float*, const int32_t*, int, int, double, const float*, float*, hipStream_t);
+template void launch_dense<double>(const double*, const int32_t*, int, int, double, const double*, double*,
+                                   hipStream_t);
+
+namespace {
+// the smoother's coefficients (Saad, Alg. 12.1 on [lam / 15, lam]) as the separate kernels take them
 template <typename T>
-bool launch_vcycle_tail(const DevLevel& L, const DevLevel& Lc, const T* minv, const T* Ainv, const int32_t* fd,
-                        int nfree, double lam, const T* b, T* x, hipStream_t s) {
-  if (!(L.uniform && !L.q3 && !L.noflux && L.n_edge == kTailN && Lc.uniform && Lc.n_edge == kTailN / 2 &&
-        nfree == kTailFree))
-    return false;
-  // the smoother's coefficients (Saad, Alg. 12.1 on [lam / 15, lam]) as the separate kernels take them
+TailCoef<T> tail_coef(double lam) {
   const double lo = lam / 15.0, theta = 0.5 * (lam + lo), delta = 0.5 * (lam - lo), sigma = theta / delta;
   TailCoef<T> cf{};
   cf.it0 = T(1.0 / theta);
@@ -2459,7 +2540,33 @@ bool launch_vcycle_tail(const DevLevel& L, const DevLevel& Lc, const T* minv, co
     cf.beta[k] = T(2.0 * rho_new / delta);
     rho = rho_new;
   }
-  k_vcycle_tail<T><<<1, 256, 0, s>>>(mu_of<T>(L), minv, Ainv, fd, cf, b, x);
+  return cf;
+}
+}  // namespace
+
+double launch_tail_columns(const TailMaps& tm, bool noflux, const double* mu, const double* minv, const double* Ainv,
+                           const int32_t* fd, double lam, double* V, hipStream_t s) {
+  const TailCoef<double> cf = tail_coef<double>(lam);
+  if (noflux)
+    k_vcycle_tail<double, true, true><<<unsigned(tm.nfree), 256, 0, s>>>(mu, minv, Ainv, fd, cf, nullptr, V, tm);
+  else
+    k_vcycle_tail<double, true, false><<<unsigned(tm.nfree), 256, 0, s>>>(mu, minv, Ainv, fd, cf, nullptr, V, tm);
+  // the cycle on a constrained dof (identity row, no coarse correction)
+  double x = cf.it0, d = x;
+  for (int k = 1; k < 4; ++k) d = cf.alpha[k] * d + cf.beta[k] * (1.0 - x), x += d;
+  d = cf.it0 * (1.0 - x), x += d;
+  for (int k = 1; k < 4; ++k) d = cf.alpha[k] * d + cf.beta[k] * (1.0 - x), x += d;
+  return x;
+}
+
+template <typename T>
+bool launch_vcycle_tail(const DevLevel& L, const DevLevel& Lc, const T* minv, const T* Ainv, const int32_t* fd,
+                        int nfree, double lam, const T* b, T* x, hipStream_t s) {
+  if (!(L.uniform && !L.q3 && !L.noflux && L.n_edge == kTailN && Lc.uniform && Lc.n_edge == kTailN / 2 &&
+        nfree == kTailFree))
+    return false;
+  k_vcycle_tail<T, false, false>
+      <<<1, 256, 0, s>>>(mu_of<T>(L), minv, Ainv, fd, tail_coef<T>(lam), b, x, TailMaps{});
   return true;
 }
 template bool launch_vcycle_tail<float>(const DevLevel&, const DevLevel&, const float*, const float*, const int32_t*,
@@ -2467,7 +2574,6 @@ template bool launch_vcycle_tail<float>(const DevLevel&, const DevLevel&, const 
 template bool launch_vcycle_tail<double>(const DevLevel&, const DevLevel&, const double*, const double*,
                                          const int32_t*, int, double, const double*, double*, hipStream_t);
 
-template void launch_coarse<double>(const double*, const int32_t*, int, int, const double*, double*, hipStream_t);
 
 void launch_harmonic_mu(int64_t ncell, const double* mq, double* mu, hipStream_t s) {
   k_harmonic<<<grid_for(ncell), kBlock, 0, s>>>(ncell, mq, mu);
