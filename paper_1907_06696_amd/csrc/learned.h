@@ -55,10 +55,11 @@ void launch_features(int64_t ncell, const int32_t* nbr, const int32_t* self, con
                      hipStream_t s);
 // MLP over n samples (x: [n][27], y: [n][3], cache: [n][131])
 void launch_mlp_forward(const float* w, const float* x, int64_t n, float* y, float* cache, hipStream_t s);
-// gradient of sum(dy * y) w.r.t. the parameters; work >= n * 260 floats,
-// part >= ceil(n / 64) * 6147 floats
+// gradient of sum(dy * y) w.r.t. the parameters; work (mlp_work_size(n)
+// floats) takes ceil(ceil(n / 16) / 2) <= ceil(n / 64) + 260 n / 6147 partials
+inline int64_t mlp_work_size(int64_t n) { return 260 * n + ((n + 63) / 64) * kParams; }
 void launch_mlp_backward(const float* w, const float* x, const float* cache, const float* dy, int64_t n, float* dw,
-                         float* work, float* part, hipStream_t s);
+                         float* work, hipStream_t s);
 // dy = scale (y - t) over n3 entries; loss[0] += sum (y - t)^2 (double)
 void launch_mse(int64_t n3, const float* y, const float* t, float* dy, float scale, double* loss, hipStream_t s);
 // dst[i][:] = src[idx[i]][:] (cols floats per row)

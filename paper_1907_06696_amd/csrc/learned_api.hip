@@ -512,12 +512,11 @@ int mfgmg_mlp_forward(const float* w, const float* x, int64_t n, float* y, float
 int mfgmg_mlp_backward(const float* w, const float* x, const float* cache, const float* dy, int64_t n, float* dw,
                        float* work, void* stream) {
   if (!w || !x || !cache || !dy || !dw || !work || n < 1) return MFGMG_ERR_INVALID;
-  float* part = work + 260 * n;
-  launch_mlp_backward(w, x, cache, dy, n, dw, work, part, static_cast<hipStream_t>(stream));
+  launch_mlp_backward(w, x, cache, dy, n, dw, work, static_cast<hipStream_t>(stream));
   return hipGetLastError() == hipSuccess ? MFGMG_OK : MFGMG_ERR_HIP;
 }
 
-int64_t mfgmg_mlp_work_size(int64_t n) { return 260 * n + ((n + 63) / 64) * kParams; }
+int64_t mfgmg_mlp_work_size(int64_t n) { return mlp_work_size(n); }
 
 int mfgmg_mlp_adam(float* w, const float* dw, float* m, float* v, int64_t step, double lr, void* stream) {
   if (!w || !dw || !m || !v || step < 1 || !(lr > 0)) return MFGMG_ERR_INVALID;
@@ -569,7 +568,7 @@ int mfgmg_mlp_train(float* w, const float* feats, const float* targets, int64_t 
       launch_gather_rows(targets, kOut, idx + b0, nb, tb, s);
       launch_mlp_forward(w, xb, nb, yb, cache, s);
       launch_mse(nb * kOut, yb, tb, dy, 2.0f / float(nb * kOut), loss, s);
-      launch_mlp_backward(w, xb, cache, dy, nb, dw, work, work + 260 * nb, s);
+      launch_mlp_backward(w, xb, cache, dy, nb, dw, work, s);
       ++step;
       launch_adam<float>(kParams, w, dw, m, v, lr, 0.9, 0.999, 1e-8, step, 0.0, s);
     }
