@@ -1553,8 +1553,7 @@ int mfgmg_apply_grad(mfgmg_ctx* ctx, const double* p, double* u_out, void* strea
   if (!ctx->mu_ready) return ctx->set(MFGMG_ERR_STATE, "set_viscosity first");
   const DevLevel& v = ctx->lv[size_t(ctx->mesh->L())].v;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  launch_fill(3 * v.nnode, 0.0, u_out, s);
-  launch_grad_add(v, ctx->pres, p, u_out, s);
+  launch_grad(v, ctx->pres, p, u_out, s);
   HIPCHK(hipGetLastError());
   return MFGMG_OK;
 }

@@ -299,6 +299,8 @@ struct DevPressure {
 };
 void launch_div(const DevLevel& L, const DevPressure& P, const double* u, double* p_out, hipStream_t s);
 void launch_grad_add(const DevLevel& L, const DevPressure& P, const double* p, double* u_out, hipStream_t s);
+// u_out = B^T p (constrained entries 0)
+void launch_grad(const DevLevel& L, const DevPressure& P, const double* p, double* u_out, hipStream_t s);
 // u_out = src + B^T p (src and u_out distinct)
 void launch_grad_from(const DevLevel& L, const DevPressure& P, const double* p, const double* src, double* u_out,
                       hipStream_t s);

@@ -1841,6 +1841,111 @@ __global__ __launch_bounds__(64) void k_grad_blocks(DevBlocks blk, DevLevel L, D
   }
 }
 
+// B u on a uniform leaf, the transpose of the stencil below: along its own
+// axis velocity component c meets pressure point P with the derivative
+// weights (-1/6, -2/3, 0, 2/3, 1/6) at nodes 2P - 2 .. 2P + 2, along the other
+// axes with the mass weights (0, 1/3, 1/3, 1/3, 0).  A wave takes one row of up
+// to 73 pressure points along x and marches along z through 2 tz + 3 planes
+// of velocity nodes (lane: words of the row, the next plane's loads in flight).
+// A plane's five rows are contracted along y as they arrive and added to the
+// three pressure planes that see them; a finished plane's row goes through LDS
+// for the contraction along x.  No workgroup barriers, no atomics, no cleared
+// output.  64^3: cell blocks with atomics into cleared output 50.5 -> 25 us;
+// marching with whole planes in LDS, two barriers a plane, 31 us.
+constexpr int kDivK = 7, kDivTX = (64 * kDivK / 3 - 3) / 2;
+__global__ __launch_bounds__(256) void k_div_uniform(int n, int nbx, int tz, DevPressure P,
+                                                     const double* __restrict__ u, double* __restrict__ po) {
+  __shared__ double rows[4][64 * kDivK];
+  const int m = 2 * n + 1, np1 = n + 1, lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  const int tx = (np1 + nbx - 1) / nbx;   // pressure points of a row
+  const int nby = (np1 + 3) / 4;
+  const int blk = int(brick::xcd_order(blockIdx.x, gridDim.x));
+  const int P0 = blk % nbx * tx, Q = blk / nbx % nby * 4 + wv, R0 = blk / (nbx * nby) * tz;
+  if (Q >= np1) return;   // a whole wave; the others do not wait for it
+  double* row = rows[wv];
+  const int64_t plane = 3 * int64_t(m) * m;
+  int off[kDivK];
+  bool in[kDivK];
+#pragma unroll
+  for (int k = 0; k < kDivK; ++k) {
+    const int w = lane + 64 * k, X = 2 * P0 - 2 + w / 3;
+    in[k] = X > 0 && X < m - 1;   // boundary values count zero
+    off[k] = in[k] ? 3 * X + w % 3 : 0;
+  }
+  // weights of word lane + 64 k, by its component (lane + k) mod 3: along y for
+  // the rows (+-2, +-1, -1 0 1), along z for an odd plane (into the current and
+  // the next pressure plane) and an even one (previous and, negated, next; current)
+  double wt[3][7];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int c = (lane + k) % 3;
+    wt[k][0] = c == 1 ? 1.0 / 6.0 : 0.0, wt[k][1] = c == 1 ? 2.0 / 3.0 : 0.0, wt[k][2] = c == 1 ? 0.0 : 1.0 / 3.0;
+    wt[k][3] = c == 2 ? 2.0 / 3.0 : 1.0 / 3.0, wt[k][4] = c == 2 ? -2.0 / 3.0 : 1.0 / 3.0;
+    wt[k][5] = c == 2 ? 1.0 / 6.0 : 0.0, wt[k][6] = c == 2 ? 0.0 : 1.0 / 3.0;
+  }
+  double v[5][kDivK];
+  auto load = [&](int j) {
+    const int Z = 2 * R0 - 2 + j;
+#pragma unroll
+    for (int r = 0; r < 5; ++r) {
+      const int Y = 2 * Q - 2 + r;
+      if (Z > 0 && Z < m - 1 && Y > 0 && Y < m - 1) {
+        const double* ur = u + plane * Z + 3 * int64_t(m) * Y;
+#pragma unroll
+        for (int k = 0; k < kDivK; ++k) v[r][k] = ur[off[k]];
+      } else {
+#pragma unroll
+        for (int k = 0; k < kDivK; ++k) v[r][k] = 0.0;
+      }
+    }
+  };
+  const double h2 = 1.0 / double(int64_t(n) * n);
+  double prev[kDivK], cur[kDivK], next[kDivK], yc[kDivK];   // pressure planes R0 - 2 + q, R0 - 1 + q, R0 + q of pair q
+#pragma unroll
+  for (int k = 0; k < kDivK; ++k) prev[k] = cur[k] = next[k] = 0.0;
+  const int NP = 2 * tz + 3;
+  load(0);
+#pragma unroll 1
+  for (int j = 0; j < NP; ++j) {
+#pragma unroll
+    for (int k = 0; k < kDivK; ++k) {
+      const double* w = wt[k % 3];
+      const double q = w[0] * (v[4][k] - v[0][k]) + w[1] * (v[3][k] - v[1][k]) + w[2] * ((v[1][k] + v[3][k]) + v[2][k]);
+      yc[k] = in[k] ? q : 0.0;
+    }
+    if (j + 1 < NP) load(j + 1);
+    if (j & 1) {
+#pragma unroll
+      for (int k = 0; k < kDivK; ++k) {
+        prev[k] = cur[k] + wt[k % 3][3] * yc[k];
+        cur[k] = next[k] + wt[k % 3][4] * yc[k];
+        next[k] = 0.0;
+      }
+      continue;
+    }
+#pragma unroll
+    for (int k = 0; k < kDivK; ++k) {
+      prev[k] += wt[k % 3][5] * yc[k];
+      cur[k] += wt[k % 3][6] * yc[k];
+      next[k] -= wt[k % 3][5] * yc[k];
+    }
+    const int R = R0 - 2 + j / 2;   // complete
+    if (R < R0 || R >= np1) continue;
+#pragma unroll
+    for (int k = 0; k < kDivK; ++k) row[lane + 64 * k] = prev[k];
+    wave_lds_sync();
+    for (int l = lane; l < tx; l += 64)
+      if (P0 + l < np1) {
+        const double* r = row + 6 * l;
+        const double s = (r[12] - r[0]) * (1.0 / 6.0) + (r[9] - r[3]) * (2.0 / 3.0) +
+                         ((r[4] + r[7] + r[10]) + (r[5] + r[8] + r[11])) * (1.0 / 3.0);
+        po[P.plat[P0 + l + np1 * (Q + int64_t(np1) * R)]] = -h2 * s;
+      }
+    wave_lds_sync();   // the row is read before the next one is stored
+  }
+}
+
 // B^T p added into uo on a uniform leaf, gathered per velocity node (no
 // atomics), by sum factorisation: with B_qj = -int psi_q div phi_j and both
 // bases tensor products, the coupling of Q2 node X and Q1 node P is, per
@@ -1849,92 +1954,108 @@ __global__ __launch_bounds__(64) void k_grad_blocks(DevBlocks blk, DevLevel L, D
 // (G1 = [[-5/6, 2/3, 1/6], [-1/6, -2/3, 5/6]]).  Assembled over the cells
 // around a node, an odd coordinate X = 2i+1 couples to P = i, i+1 with mass
 // (1/3, 1/3) and derivative (2/3, -2/3); an even X = 2i to P = i-1, i, i+1
-// with mass (0, 1/3, 0) and derivative (1/6, 0, -1/6).  The node reads the
-// <= 27 pressure values of its 3x3x3 lattice window and contracts them axis
-// by axis; the cell size enters as h^2.
-// A workgroup takes a 16 x 4 x 4 tile of velocity nodes and first stages the
-// pressure values of the lattice window its nodes read (11 x 5 x 5 points,
-// 0 off the lattice) in LDS.
-// FROM: uo = src + B^T p (every node written; src may not alias uo),
-// otherwise uo += B^T p.
-constexpr int kGradTX = 16, kGradTY = 4, kGradTZ = 4;
-template <bool FROM>
-__global__ __launch_bounds__(kGradTX * kGradTY * kGradTZ) void k_grad_uniform(int64_t n, DevPressure P,
-                                                                            const double* __restrict__ p,
-                                                                            const double* __restrict__ src,
-                                                                            double* __restrict__ uo) {
-  constexpr int NT = kGradTX * kGradTY * kGradTZ;
-  constexpr int WX = kGradTX / 2 + 3, WY = kGradTY / 2 + 3, WZ = kGradTZ / 2 + 3;
+// with mass (0, 1/3, 0) and derivative (1/6, 0, -1/6).  The cell size enters
+// as h^2.
+// A thread takes the eight nodes 2i, 2i + 1 (per axis) of lattice point i: they
+// read one 3 x 3 x 3 pressure window, contracted axis by axis for both
+// parities, about 90 operations for the eight where a thread per node took
+// 130 for one.  A workgroup's 32 x 4 x 2 points leave their 64 x 8 x 4 nodes in
+// LDS and the node rows go out coalesced, one wave a row; the closing planes
+// (Dirichlet) belong to the last workgroups along an axis.
+// OUT: Add uo += B^T p; Set uo = B^T p (every node written, so no clearing
+// pass and no read of uo); From uo = src + B^T p (src may not alias uo).
+// 64^3, Set: cleared output and a thread per node 43.6 -> 21 us.
+constexpr int kGradTX = 32, kGradTY = 4, kGradTZ = 2, kGradThreads = kGradTX * kGradTY * kGradTZ;
+enum class GradOut { Add, Set, From };
+template <GradOut OUT>
+__global__ __launch_bounds__(kGradThreads) void k_grad_uniform(int n, DevPressure P, const double* __restrict__ p,
+                                                               const double* __restrict__ src,
+                                                               double* __restrict__ uo) {
+  constexpr int WX = kGradTX + 2, WY = kGradTY + 2, WZ = kGradTZ + 2, ROW = 6 * kGradTX;
   __shared__ double sp[WZ * WY * WX];
-  const int64_t m = 2 * n + 1, np1 = n + 1;
-  const int64_t ntx = (m + kGradTX - 1) / kGradTX, nty = (m + kGradTY - 1) / kGradTY;
-  const int64_t tile = blockIdx.x;
-  const int64_t X0 = (tile % ntx) * kGradTX, Y0 = ((tile / ntx) % nty) * kGradTY, Z0 = (tile / (ntx * nty)) * kGradTZ;
-  // the first window point of each axis: the lowest P0 = (X - 1) / 2 of the
-  // tile's interior nodes
-  const int64_t q0[3] = {X0 > 0 ? (X0 - 1) / 2 : 0, Y0 > 0 ? (Y0 - 1) / 2 : 0, Z0 > 0 ? (Z0 - 1) / 2 : 0};
-  for (int e = threadIdx.x; e < WX * WY * WZ; e += NT) {
-    const int64_t px = q0[0] + e % WX, py = q0[1] + (e / WX) % WY, pz = q0[2] + e / (WX * WY);
-    sp[e] = px < np1 && py < np1 && pz < np1 ? p[P.plat[px + np1 * (py + np1 * pz)]] : 0.0;
+  __shared__ double out[4 * kGradTY * kGradTZ][ROW];
+  const int m = 2 * n + 1, np1 = n + 1, t = threadIdx.x;
+  const int ntx = (n + kGradTX - 1) / kGradTX, nty = (n + kGradTY - 1) / kGradTY, ntz = (n + kGradTZ - 1) / kGradTZ;
+  const int tile = int(brick::xcd_order(blockIdx.x, gridDim.x));
+  const int tx = tile % ntx, ty = tile / ntx % nty, tz = tile / (ntx * nty);
+  const int I0 = tx * kGradTX, J0 = ty * kGradTY, K0 = tz * kGradTZ;
+  for (int e = t; e < WX * WY * WZ; e += kGradThreads) {
+    const int px = I0 - 1 + e % WX, py = J0 - 1 + e / WX % WY, pz = K0 - 1 + e / (WX * WY);
+    const bool in = px >= 0 && py >= 0 && pz >= 0 && px < np1 && py < np1 && pz < np1;
+    sp[e] = in ? p[P.plat[px + np1 * (py + int64_t(np1) * pz)]] : 0.0;
   }
   __syncthreads();
-  const double h2 = 1.0 / double(n * n);
-  const int64_t X[3] = {X0 + int(threadIdx.x) % kGradTX, Y0 + (int(threadIdx.x) / kGradTX) % kGradTY,
-                        Z0 + int(threadIdx.x) / (kGradTX * kGradTY)};
-  if (X[0] >= m || X[1] >= m || X[2] >= m) return;
-  const int64_t v = X[0] + m * (X[1] + m * X[2]);
-  if (X[0] == 0 || X[1] == 0 || X[2] == 0 || X[0] == m - 1 || X[1] == m - 1 || X[2] == m - 1) {
-    if (FROM) uo[3 * v] = src[3 * v], uo[3 * v + 1] = src[3 * v + 1], uo[3 * v + 2] = src[3 * v + 2];
-    return;
-  }
-  int o[3];   // window offset of the node's first pressure point per axis
-  double wm[3][3], wg[3][3];
+  {
+    const int i = t % kGradTX, j = t / kGradTX % kGradTY, k = t / (kGradTX * kGradTY);
+    const double* w = sp + i + WX * (j + WY * k);
+    const double h2 = -1.0 / double(int64_t(n) * n);
+    // mass and derivative weights of the even (par 0) and the odd node over
+    // the window's three points
+    auto mass = [](int par, double, double b, double c) { return par ? (b + c) * (1.0 / 3.0) : b * (1.0 / 3.0); };
+    auto derv = [](int par, double a, double b, double c) {
+      return par ? (b - c) * (2.0 / 3.0) : (a - c) * (1.0 / 6.0);
+    };
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    o[d] = int((X[d] - 1) / 2 - q0[d]);
-    if (X[d] & 1) {
-      wm[d][0] = 1.0 / 3.0, wm[d][1] = 1.0 / 3.0, wm[d][2] = 0.0;
-      wg[d][0] = 2.0 / 3.0, wg[d][1] = -2.0 / 3.0, wg[d][2] = 0.0;
-    } else {
-      wm[d][0] = 0.0, wm[d][1] = 1.0 / 3.0, wm[d][2] = 0.0;
-      wg[d][0] = 1.0 / 6.0, wg[d][1] = 0.0, wg[d][2] = -1.0 / 6.0;
+    for (int pz = 0; pz < 2; ++pz) {
+      double zm[3][3], zg[3][3];   // [y][x] contracted along z with mass / derivative weights
+#pragma unroll
+      for (int b = 0; b < 3; ++b)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const double w0 = w[a + WX * b], w1 = w[a + WX * (b + WY)], w2 = w[a + WX * (b + 2 * WY)];
+          zm[b][a] = mass(pz, w0, w1, w2);
+          zg[b][a] = derv(pz, w0, w1, w2);
+        }
+#pragma unroll
+      for (int py = 0; py < 2; ++py) {
+        double ymm[3], ygm[3], ymg[3];   // then along y: (y, z) mass/mass, derivative/mass, mass/derivative
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          ymm[a] = mass(py, zm[0][a], zm[1][a], zm[2][a]);
+          ygm[a] = derv(py, zm[0][a], zm[1][a], zm[2][a]);
+          ymg[a] = mass(py, zg[0][a], zg[1][a], zg[2][a]);
+        }
+        double* o = out[2 * j + py + 2 * kGradTY * (2 * k + pz)] + 6 * i;
+#pragma unroll
+        for (int px = 0; px < 2; ++px) {
+          o[3 * px] = h2 * derv(px, ymm[0], ymm[1], ymm[2]);
+          o[3 * px + 1] = h2 * mass(px, ygm[0], ygm[1], ygm[2]);
+          o[3 * px + 2] = h2 * mass(px, ymg[0], ymg[1], ymg[2]);
+        }
+      }
     }
   }
-  double zm[3][3], zg[3][3];   // contracted along z with mass / derivative weights
+  __syncthreads();
+  // node rows of the tile and, on the last tiles, of the closing planes
+  const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int nx = min(2 * kGradTX, 2 * (n - I0)) + (tx == ntx - 1), ny = min(2 * kGradTY, 2 * (n - J0)) + (ty == nty - 1);
+  const int nz = min(2 * kGradTZ, 2 * (n - K0)) + (tz == ntz - 1);
+  for (int r = wv; r < ny * nz; r += kGradThreads / 64) {
+    const int ly = r % ny, lz = r / ny, Y = 2 * J0 + ly, Z = 2 * K0 + lz;
+    const bool wall = Y == 0 || Z == 0 || Y == m - 1 || Z == m - 1;
+    const int64_t g = 3 * (2 * I0 + m * (Y + int64_t(m) * Z));
+    const double* o = out[wall ? 0 : ly + 2 * kGradTY * lz];
+    constexpr int KW = (ROW + 3 + 63) / 64;
+    double old[KW];
 #pragma unroll
-  for (int b = 0; b < 3; ++b)
+    for (int q = 0; q < KW; ++q) {
+      const int e = lane + 64 * q;
+      old[q] = 0.0;
+      if (OUT != GradOut::Set && e < 3 * nx) old[q] = OUT == GradOut::From ? src[g + e] : uo[g + e];
+    }
 #pragma unroll
-    for (int a = 0; a < 3; ++a) zm[b][a] = zg[b][a] = 0.0;
-#pragma unroll
-  for (int c = 0; c < 3; ++c)
-#pragma unroll
-    for (int b = 0; b < 3; ++b)
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const double val = sp[(o[2] + c) * (WY * WX) + (o[1] + b) * WX + o[0] + a];
-        zm[b][a] += wm[2][c] * val;
-        zg[b][a] += wg[2][c] * val;
-      }
-  double ymm[3], ygm[3], ymg[3];   // then along y: (y, z) weights mass/mass, deriv/mass, mass/deriv
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    ymm[a] = wm[1][0] * zm[0][a] + wm[1][1] * zm[1][a] + wm[1][2] * zm[2][a];
-    ygm[a] = wg[1][0] * zm[0][a] + wg[1][1] * zm[1][a] + wg[1][2] * zm[2][a];
-    ymg[a] = wm[1][0] * zg[0][a] + wm[1][1] * zg[1][a] + wm[1][2] * zg[2][a];
-  }
-  const double g0 = wg[0][0] * ymm[0] + wg[0][1] * ymm[1] + wg[0][2] * ymm[2];
-  const double g1 = wm[0][0] * ygm[0] + wm[0][1] * ygm[1] + wm[0][2] * ygm[2];
-  const double g2 = wm[0][0] * ymg[0] + wm[0][1] * ymg[1] + wm[0][2] * ymg[2];
-  if (FROM) {
-    uo[3 * v] = src[3 * v] - h2 * g0, uo[3 * v + 1] = src[3 * v + 1] - h2 * g1;
-    uo[3 * v + 2] = src[3 * v + 2] - h2 * g2;
-  } else {
-    uo[3 * v] -= h2 * g0, uo[3 * v + 1] -= h2 * g1, uo[3 * v + 2] -= h2 * g2;
+    for (int q = 0; q < KW; ++q) {
+      const int e = lane + 64 * q, X = 2 * I0 + e / 3;
+      if (e >= 3 * nx) continue;
+      const bool dir = wall || X == 0 || X == m - 1;
+      if (OUT == GradOut::Add && dir) continue;
+      uo[g + e] = dir ? old[q] : old[q] + o[min(e, ROW - 1)];
+    }
   }
 }
+
 unsigned grad_uniform_tiles(int64_t n) {
-  const int64_t m = 2 * n + 1;
-  return unsigned(((m + kGradTX - 1) / kGradTX) * ((m + kGradTY - 1) / kGradTY) * ((m + kGradTZ - 1) / kGradTZ));
+  return unsigned(((n + kGradTX - 1) / kGradTX) * ((n + kGradTY - 1) / kGradTY) * ((n + kGradTZ - 1) / kGradTZ));
 }
 
 // M_p p on a uniform leaf of n^3 cells, one thread per Q1 lattice point (no
@@ -2659,6 +2780,18 @@ void launch_mul(int64_t n, const double* a, const double* b, double* y, hipStrea
 }
 
 void launch_div(const DevLevel& L, const DevPressure& P, const double* u, double* po, hipStream_t s) {
+  if (L.uniform && P.plat) {   // every pressure node is written
+    const int64_t np1 = L.n_edge + 1;
+    const int64_t nbx = (np1 + kDivTX - 1) / kDivTX, nby = (np1 + 3) / 4;
+    // A wave works alone for 2 tz + 3 planes, so the count of waves against the
+    // 1,024 SIMDs sets the time: the shortest march that still leaves one wave
+    // a SIMD (64^3: tz = 5, 884 waves, 24 us; tz = 4, 1,156 waves, 33 us), else 8
+    int64_t tz = 2;
+    while (tz < 8 && 4 * nbx * nby * ((np1 + tz - 1) / tz) > 1024) ++tz;
+    k_div_uniform<<<unsigned(nbx * nby * ((np1 + tz - 1) / tz)), 256, 0, s>>>(int(L.n_edge), int(nbx), int(tz), P, u,
+                                                                             po);
+    return;
+  }
   k_fill<<<grid_for(P.np), kBlock, 0, s>>>(P.np, 0.0, po);
   if (L.q3) {
     launch_div_q3(L, u, po, s);
@@ -2676,19 +2809,28 @@ void launch_div(const DevLevel& L, const DevPressure& P, const double* u, double
 void launch_grad_from(const DevLevel& L, const DevPressure& P, const double* p, const double* src, double* uo,
                       hipStream_t s) {
   if (L.uniform) {
-    k_grad_uniform<true><<<grad_uniform_tiles(L.n_edge), kGradTX * kGradTY * kGradTZ, 0, s>>>(L.n_edge, P, p, src,
-                                                                                              uo);
+    k_grad_uniform<GradOut::From>
+        <<<grad_uniform_tiles(L.n_edge), kGradThreads, 0, s>>>(int(L.n_edge), P, p, src, uo);
     return;
   }
   (void)hipMemcpyAsync(uo, src, size_t(3 * L.nnode) * sizeof(double), hipMemcpyDeviceToDevice, s);
+  launch_grad_add(L, P, p, uo, s);
+}
+void launch_grad(const DevLevel& L, const DevPressure& P, const double* p, double* uo, hipStream_t s) {
+  if (L.uniform) {
+    k_grad_uniform<GradOut::Set>
+        <<<grad_uniform_tiles(L.n_edge), kGradThreads, 0, s>>>(int(L.n_edge), P, p, nullptr, uo);
+    return;
+  }
+  launch_fill(3 * L.nnode, 0.0, uo, s);
   launch_grad_add(L, P, p, uo, s);
 }
 void launch_grad_add(const DevLevel& L, const DevPressure& P, const double* p, double* uo, hipStream_t s) {
   if (L.q3) {
     launch_grad_q3(L, p, uo, s);
   } else if (L.uniform) {
-    k_grad_uniform<false><<<grad_uniform_tiles(L.n_edge), kGradTX * kGradTY * kGradTZ, 0, s>>>(L.n_edge, P, p,
-                                                                                               nullptr, uo);
+    k_grad_uniform<GradOut::Add>
+        <<<grad_uniform_tiles(L.n_edge), kGradThreads, 0, s>>>(int(L.n_edge), P, p, nullptr, uo);
   } else if (L.blk4.n || L.blk2.n) {
     double* fs = L.fslot_d;
     if (L.blk4.n) k_grad_blocks<4><<<unsigned(L.blk4.n), 64, 0, s>>>(L.blk4, L, P, p, uo, fs);
