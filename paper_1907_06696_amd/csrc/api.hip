@@ -229,6 +229,21 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
   v.noflux = !h.fixmask.empty();
   if (v.noflux && h.nnode > int64_t(kSlotNodeMask))
     return ctx->set(MFGMG_ERR_MESH, "no-normal-flux levels are limited to 2^28 nodes");
+  // every cell of the level's size present: run as a grid
+  const int64_t edge = int64_t(1) << std::min(h.ell, 16);
+  if (v.noflux && edge >= 2 && edge <= kGridMaxEdge && h.ncell == edge * edge * edge) {
+    const int64_t mm = 2 * edge + 1;
+    std::vector<int32_t> node(static_cast<size_t>(mm * mm * mm)), cell(static_cast<size_t>(h.ncell));
+    for (int64_t c = 0; c < h.ncell; ++c) {
+      const int64_t i = h.cijk[size_t(3 * c)], j = h.cijk[size_t(3 * c + 1)], k = h.cijk[size_t(3 * c + 2)];
+      cell[size_t(i + edge * (j + edge * k))] = int32_t(c);
+      for (int a = 0; a < 27; ++a)
+        node[size_t(2 * i + a % 3 + mm * (2 * j + a / 3 % 3 + mm * (2 * k + a / 9)))] = h.cell_nodes[size_t(27 * c + a)];
+    }
+    v.grid_edge = edge;
+    v.grid_node = ctx->upload(node);
+    v.grid_cell = ctx->upload(cell);
+  }
   // a free slot with the node's fixed components in its top bits (no-normal-
   // flux levels; the slot itself otherwise)
   auto encode = [&](std::vector<int32_t> sl) {

@@ -50,12 +50,20 @@ struct DevBlocks {
   const double* phw = nullptr;
 };
 
+constexpr int64_t kGridMaxEdge = 32;
 // Device view of one level mesh.
 struct DevLevel {
   int ell = 0;
   int64_t ncell = 0, nnode = 0;
   bool uniform = false;
   int64_t n_edge = 0;
+  // levels under u . n = 0 whose cells are all of the level's size, up to
+  // kGridMaxEdge cells per edge: stored as general levels, run by the small
+  // uniform levels' kernel through the storage node and cell of each lattice
+  // node and cell (grid_edge: cells per edge, 0 elsewhere)
+  int64_t grid_edge = 0;
+  const int32_t* grid_node = nullptr;
+  const int32_t* grid_cell = nullptr;
   // general (non-uniform) levels
   const int32_t* slots = nullptr;   // [27*ncell]: node >= 0 free, -1 Dirichlet, -(2+h) hanging row h
   const int8_t* clev = nullptr;     // [ncell]
@@ -180,14 +188,14 @@ template <typename T>
 void launch_chebx_step(int64_t n, const T* b, const T* t, const T* minv, T* d, T* x, double alpha, double beta,
                        hipStream_t s, const ChebPrep& p = ChebPrep());
 // true when launch_vmult on L starts with an output initialisation kernel
-// (the general levels)
+// (the general levels but those run as a grid)
 bool vmult_has_init(const DevLevel& L);
 // y = A x like launch_vmult (init), for a y already holding x on the
 // constrained dofs and 0 elsewhere (the initialisation kernel is skipped)
 template <typename T>
 void launch_vmult_prepared(const DevLevel& L, const T* x, T* y, hipStream_t s);
 
-// Uniform levels up to 32^3 cells: the smoother's update and the residual
+// Uniform levels and grid levels up to 32^3 cells: the smoother's update and the residual
 // formed inside the operator's kernel.  y must be neither x nor b.
 //   first: x0 = d0 = it0 minv b (not stored), then d = alpha d0 + beta minv
 //   (b - A x0), y = x0 + d; step: d = alpha d + beta minv (b - A x), y = x + d

@@ -2457,14 +2457,18 @@ void launch_brick(const DevLevel& L, const T* x, T* y, T* halo, bool init, hipSt
 template <owner::Op OP, typename T>
 void launch_owner(const DevLevel& L, const T* x, const T* b, const T* minv, T* d, T* y, double alpha, double beta,
                   double it0, hipStream_t s) {
-  const int64_t n = L.n_edge;
-  const owner::Args<T> a{int(n), mu_of<T>(L), x, b, minv, d, y, T(alpha), T(beta), T(it0)};
-  if (n <= 16) {
-    owner::k_owner<T, 1, int, OP><<<unsigned(n * n * n / 8), owner::kThreads, 0, s>>>(a);
+  const int64_t n = L.uniform ? L.n_edge : L.grid_edge;
+  const owner::Args<T> a{int(n), mu_of<T>(L), x, b, minv, d, y, T(alpha), T(beta), T(it0), L.grid_node, L.grid_cell};
+  const unsigned g1 = unsigned(n * n * n / 8), g2 = unsigned(n * n * n / 16);
+  if (!L.uniform) {
+    if (n <= 16) owner::k_owner<T, 1, int, true, OP><<<g1, owner::kThreads, 0, s>>>(a);
+    else owner::k_owner<T, 2, int, true, OP><<<g2, owner::kThreads, 0, s>>>(a);
+  } else if (n <= 16) {
+    owner::k_owner<T, 1, int, false, OP><<<g1, owner::kThreads, 0, s>>>(a);
   } else if (n <= kFusedMaxEdge) {
-    owner::k_owner<T, 2, int, OP><<<unsigned(n * n * n / 16), owner::kThreads, 0, s>>>(a);
+    owner::k_owner<T, 2, int, false, OP><<<g2, owner::kThreads, 0, s>>>(a);
   } else if constexpr (OP == owner::Op::Apply || OP == owner::Op::Add) {   // beyond the brick kernel's index range
-    owner::k_owner<T, 2, int64_t, OP><<<unsigned(n * n * n / 16), owner::kThreads, 0, s>>>(a);
+    owner::k_owner<T, 2, int64_t, false, OP><<<g2, owner::kThreads, 0, s>>>(a);
   }
 }
 
@@ -2481,6 +2485,11 @@ void vmult_impl(const DevLevel& L, const T* x, T* y, hipStream_t s, bool init, b
     } else {
       launch_owner<owner::Op::Add, T>(L, x, nullptr, nullptr, nullptr, y, 0.0, 0.0, 0.0, s);
     }
+    return;
+  }
+  if (L.grid_edge) {
+    if (init) launch_owner<owner::Op::Apply, T>(L, x, nullptr, nullptr, nullptr, y, 0.0, 0.0, 0.0, s);
+    else launch_owner<owner::Op::Add, T>(L, x, nullptr, nullptr, nullptr, y, 0.0, 0.0, 0.0, s);
     return;
   }
   if (L.q3) {   // owner-computes: no initialisation kernel (vmult_has_init is false)
@@ -2518,9 +2527,9 @@ template <typename T>
 void launch_vmult_prepared(const DevLevel& L, const T* x, T* y, hipStream_t s) {
   vmult_impl<T>(L, x, y, s, true, true);
 }
-bool vmult_has_init(const DevLevel& L) { return !L.q3 && !L.uniform; }
+bool vmult_has_init(const DevLevel& L) { return !L.q3 && !L.uniform && !L.grid_edge; }
 
-bool smoother_fuses(const DevLevel& L) { return L.uniform && L.n_edge <= kFusedMaxEdge; }
+bool smoother_fuses(const DevLevel& L) { return L.grid_edge || (L.uniform && L.n_edge <= kFusedMaxEdge); }
 template <typename T>
 void launch_fused_first(const DevLevel& L, const T* b, const T* minv, T* d, T* y, double it0, double alpha,
                         double beta, hipStream_t s) {

@@ -49,6 +49,9 @@ struct Args {
   T* d;
   T* y;               // never x: neighbouring workgroups read x
   T alpha, beta, it0;
+  // MAP: storage node and cell of each lattice node and cell
+  const int32_t* node;
+  const int32_t* cell;
 };
 
 template <Op OP>
@@ -63,8 +66,11 @@ struct Brick {
 constexpr int kThreads = 192;   // wave c: component c of the cells
 // own nodes: 4 E x 4 x 4, three entries each, E a thread
 
-// I: node index type (int up to 256 cells per edge)
-template <typename T, int E, typename I, Op OP>
+// I: node index type (int up to 256 cells per edge).  MAP: a level under u . n
+// = 0 whose cells are all of one size, stored in the general order: nodes and
+// cells go through a.node and a.cell, and component c is fixed on the two
+// faces normal to axis c only.
+template <typename T, int E, typename I, bool MAP, Op OP>
 __global__ __launch_bounds__(kThreads) void k_owner(Args<T> a) {
   using S = Brick<E>;
   constexpr int BX = S::BX, CX = S::CX, C = S::C, NX = S::NX, N = S::N, kCells = S::cells;
@@ -81,19 +87,32 @@ __global__ __launch_bounds__(kThreads) void k_owner(Args<T> a) {
   const int bx = blk % nbx, by = blk / nbx % nb, bz = blk / (nbx * nb);
   const int X0 = 2 * BX * bx, Y0 = 4 * by, Z0 = 4 * bz;
   const int t = threadIdx.x;
-  // box rows, RP at a time; points on or outside the boundary
-  // stage zero (their index is 0).  Every load is issued before use.
+  // index of component q at a lattice point, and whether it is fixed
+  auto entry = [&](int X, int Y, int Z, int q) -> I {
+    const I p = X + I(m) * (Y + I(m) * Z);
+    return 3 * I(MAP ? a.node[p] : p) + q;
+  };
+  auto fixed = [&](int X, int Y, int Z, int q) {
+    if constexpr (MAP) {
+      const int w = q == 0 ? X : q == 1 ? Y : Z;
+      return w == 0 || w == m - 1;
+    }
+    return X == 0 || X == m - 1 || Y == 0 || Y == m - 1 || Z == 0 || Z == m - 1;
+  };
+  // box rows, RP at a time; fixed entries and points outside
+  // the level stage zero (their index is 0).  Every load is issued before use.
   constexpr int RW = 3 * NX, RP = kThreads / RW, NR = N * N, KS = (NR + RP - 1) / RP;
   const int word = t % RW, sx = word / 3, sq = word - 3 * sx, r0 = t / RW;
   T v[KS];
   {
     const int X = X0 - 2 + sx;
-    const bool xin = r0 < RP && X > 0 && X < m - 1;
+    const bool xin = r0 < RP && (MAP ? X >= 0 && X < m : X > 0 && X < m - 1);
 #pragma unroll
     for (int k = 0; k < KS; ++k) {
       const int r = r0 + RP * k, Y = Y0 - 2 + r % N, Z = Z0 - 2 + r / N;
-      const bool in = xin && r < NR && Y > 0 && Y < m - 1 && Z > 0 && Z < m - 1;
-      const I i = in ? 3 * (X + I(m) * (Y + I(m) * Z)) + sq : 0;
+      const bool in = xin && r < NR && (MAP ? Y >= 0 && Y < m && Z >= 0 && Z < m && !fixed(X, Y, Z, sq)
+                                            : Y > 0 && Y < m - 1 && Z > 0 && Z < m - 1);
+      const I i = in ? entry(X, Y, Z, sq) : 0;
       if constexpr (OP == Op::First) v[k] = a.minv[i] * a.b[i] * a.it0;
       else v[k] = a.x[i];
       if (!in) v[k] = T(0);
@@ -107,8 +126,8 @@ __global__ __launch_bounds__(kThreads) void k_owner(Args<T> a) {
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int X = X0 + 4 * e + t / 3 % 4;
-    own[e] = 3 * (X + I(m) * (Y0 + oy + I(m) * (Z0 + oz))) + oq;
-    dir[e] = X == 0 || Y0 + oy == 0 || Z0 + oz == 0;
+    own[e] = entry(X, Y0 + oy, Z0 + oz, oq);
+    dir[e] = MAP ? fixed(X, Y0 + oy, Z0 + oz, oq) : X == 0 || Y0 + oy == 0 || Z0 + oz == 0;
     if constexpr (OP != Op::Apply && OP != Op::Add) b[e] = a.b[own[e]];
     if constexpr (is_update<OP>) mi[e] = a.minv[own[e]];
     if constexpr (OP == Op::Step || OP == Op::Last) d[e] = a.d[own[e]];
@@ -122,7 +141,8 @@ __global__ __launch_bounds__(kThreads) void k_owner(Args<T> a) {
   const int gx = BX * bx - 1 + cx, gy = 2 * by - 1 + cy, gz = 2 * bz - 1 + cz;
   const bool cell = gx >= 0 && gy >= 0 && gz >= 0;
   // mu h; zero for cells outside the mesh, whose points are all zero
-  T mu_h = a.mu[cell ? gx + I(n) * (gy + I(n) * gz) : 0] / T(n);
+  const I mc = cell ? gx + I(n) * (gy + I(n) * gz) : 0;
+  T mu_h = a.mu[MAP ? I(a.cell[mc]) : mc] / T(n);
   if (!cell) mu_h = T(0);
 #pragma unroll
   for (int k = 0; k < KS; ++k)
@@ -150,68 +170,71 @@ __global__ __launch_bounds__(kThreads) void k_owner(Args<T> a) {
     for (int p = 0; p < 27; ++p) mem[(comp * 27 + p) * kCells + ci] = mu_h * w[p];
   }
   __syncthreads();
-  // A x of the owned entries: along each axis a point on a cell edge (even)
-  // takes node 2 of one cell and node 0 of the next, else node 1 of one
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int l[3] = {t / 3 % 4 + 4 * e + 2, oy + 2, oz + 2};
+  // A x of component q at box point l: along each axis a point on a cell edge
+  // (even) takes node 2 of one cell and node 0 of the next (not computed past
+  // the brick's last point: top), else node 1 of one
+  auto sum = [&](int q, int lx, int ly, int lz, bool top0, bool top1, bool top2) {
+    const int l[3] = {lx, ly, lz};
+    const bool top[3] = {top0, top1, top2};
     constexpr int step[3] = {1, CX, CX * C}, node[3] = {1, 3, 9};
-    int at = oq * 27 * kCells, up[3];
-    bool odd[3];
+    int at = q * 27 * kCells, up[3];
+    bool one[3];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      odd[q] = l[q] & 1;
-      at += (odd[q] ? l[q] >> 1 : (l[q] >> 1) - 1) * step[q] + (odd[q] ? 1 : 2) * node[q] * kCells;
-      up[q] = odd[q] ? 0 : step[q] - 2 * node[q] * kCells;
+    for (int e = 0; e < 3; ++e) {
+      const bool odd = l[e] & 1;
+      one[e] = odd || top[e];
+      at += (odd ? l[e] >> 1 : (l[e] >> 1) - 1) * step[e] + (odd ? 1 : 2) * node[e] * kCells;
+      up[e] = one[e] ? 0 : step[e] - 2 * node[e] * kCells;
     }
     T ax = T(0);
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
-      const T q = mem[at + ((s & 1) ? up[0] : 0) + ((s & 2) ? up[1] : 0) + ((s & 4) ? up[2] : 0)];
-      const bool use = !(((s & 1) && odd[0]) || ((s & 2) && odd[1]) || ((s & 4) && odd[2]));
-      ax += use ? q : T(0);
+      const T r = mem[at + ((s & 1) ? up[0] : 0) + ((s & 2) ? up[1] : 0) + ((s & 4) ? up[2] : 0)];
+      const bool use = !(((s & 1) && one[0]) || ((s & 2) && one[1]) || ((s & 4) && one[2]));
+      ax += use ? r : T(0);
     }
-    if (dir[e]) ax = x[e];
-    const I i = own[e];
+    return ax;
+  };
+  auto finish = [&](I i, T ax, bool fx, T xe, T be, T me, T de) {
+    if (fx) ax = xe;
     if constexpr (OP == Op::Apply) {
       a.y[i] = ax;
     } else if constexpr (OP == Op::Add) {
-      if (!dir[e]) a.y[i] = d[e] + ax;
+      if (!fx) a.y[i] = de + ax;
     } else if constexpr (OP == Op::Residual) {
-      a.y[i] = b[e] - ax;
+      a.y[i] = be - ax;
     } else {
-      T dn = a.beta * mi[e] * (b[e] - ax);
-      if constexpr (OP == Op::First) dn = a.alpha * x[e] + dn;
-      if constexpr (OP == Op::Step || OP == Op::Last) dn = a.alpha * d[e] + dn;
+      T dn = a.beta * me * (be - ax);
+      if constexpr (OP == Op::First) dn = a.alpha * xe + dn;
+      if constexpr (OP == Op::Step || OP == Op::Last) dn = a.alpha * de + dn;
       if constexpr (OP != Op::Last) a.d[i] = dn;
-      a.y[i] = x[e] + dn;
+      a.y[i] = xe + dn;
     }
-  }
-  // the closing planes (Dirichlet: A x = x) belong to the last bricks
-  if constexpr (OP != Op::Add) {
-    if (bx == nbx - 1 || by == nb - 1 || bz == nb - 1) {
-      constexpr int WX = 2 * BX + 1, W = 5;
-      for (int e = t; e < 3 * WX * W * W; e += kThreads) {
-        const int q = e % 3, lx = e / 3 % WX, ly = e / (3 * WX) % W, lz = e / (3 * WX * W);
-        const bool cx1 = lx == WX - 1, cy1 = ly == W - 1, cz1 = lz == W - 1;
-        const bool mine = (cx1 && bx == nbx - 1) || (cy1 && by == nb - 1) || (cz1 && bz == nb - 1);
-        const bool other = (cx1 && bx < nbx - 1) || (cy1 && by < nb - 1) || (cz1 && bz < nb - 1);
-        if (!mine || other) continue;
-        const I i = 3 * (X0 + lx + I(m) * (Y0 + ly + I(m) * (Z0 + lz))) + q;
-        if constexpr (OP == Op::Apply) {
-          a.y[i] = a.x[i];
-        } else if constexpr (OP == Op::Residual) {
-          a.y[i] = a.b[i] - a.x[i];
-        } else {
-          const T mb = a.minv[i], bb = a.b[i], xx = OP == Op::First ? mb * bb * a.it0 : a.x[i];
-          T dn = a.beta * mb * (bb - xx);
-          if constexpr (OP == Op::First) dn = a.alpha * xx + dn;
-          if constexpr (OP == Op::Step || OP == Op::Last) dn = a.alpha * a.d[i] + dn;
-          if constexpr (OP != Op::Last) a.d[i] = dn;
-          a.y[i] = xx + dn;
-        }
-      }
-    }
+  };
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    finish(own[e], sum(oq, t / 3 % 4 + 4 * e + 2, oy + 2, oz + 2, false, false, false), dir[e], x[e], b[e], mi[e], d[e]);
+  // the closing planes belong to the last bricks (fixed throughout under u = 0)
+  if ((OP == Op::Add && !MAP) || (bx < nbx - 1 && by < nb - 1 && bz < nb - 1)) return;
+  constexpr int WX = 2 * BX + 1, W = 5;
+  for (int e = t; e < 3 * WX * W * W; e += kThreads) {
+    const int q = e % 3, lx = e / 3 % WX, ly = e / (3 * WX) % W, lz = e / (3 * WX * W);
+    const bool c0 = lx == WX - 1, c1 = ly == W - 1, c2 = lz == W - 1;
+    const bool mine = (c0 && bx == nbx - 1) || (c1 && by == nb - 1) || (c2 && bz == nb - 1);
+    const bool other = (c0 && bx < nbx - 1) || (c1 && by < nb - 1) || (c2 && bz < nb - 1);
+    if (!mine || other) continue;
+    const I i = entry(X0 + lx, Y0 + ly, Z0 + lz, q);
+    const bool fx = fixed(X0 + lx, Y0 + ly, Z0 + lz, q);
+    T be = T(0), me = T(0), de = T(0), xe;
+    if constexpr (OP != Op::Apply && OP != Op::Add) be = a.b[i];
+    if constexpr (is_update<OP>) me = a.minv[i];
+    if constexpr (OP == Op::Step || OP == Op::Last) de = a.d[i];
+    if constexpr (OP == Op::Add) de = a.y[i];
+    if constexpr (OP == Op::First) xe = me * be * a.it0;
+    else xe = a.x[i];
+    T ax = T(0);
+    if constexpr (MAP) ax = sum(q, lx + 2, ly + 2, lz + 2, c0, c1, c2);
+    finish(i, ax, fx, xe, be, me, de);
   }
 }
 

@@ -1,4 +1,5 @@
-"""GPU: the fused kernels of the small uniform levels (2^3 to 32^3 cells).
+"""GPU: the fused kernels of the small uniform levels (2^3 to 32^3 cells), with
+u = 0 and, through node and cell maps, with u . n = 0 (free boundary nodes).
 
 One mesh of 32^3 cells, every level of it: the operator, the accumulating
 operator, and the smoother from zero and from a start, with inputs that are
@@ -19,11 +20,16 @@ pytestmark = pytest.mark.gpu
 TOL = {"float64": 1e-12, "float32": 1e-5}
 
 
+@pytest.fixture(scope="module", params=["dirichlet", "noflux"])
+def bc(request):
+    return request.param
+
+
 @pytest.fixture(scope="module")
-def case():
+def case(bc):
     import torch
     torch.cuda.set_device(0)
-    c = Case(base=5, sinkers=6, dr=1e4, seed=4)
+    c = Case(base=5, sinkers=6, dr=1e4, seed=4, bc=bc)
     c.s.set_viscosity(c.mu_qp_lib)
     yield c, omg.GMG(c.H, c.mus)
     c.close()
