@@ -397,11 +397,15 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
       std::vector<int32_t> sreg, shang;
       make_blocks(4, b4);
       make_blocks(2, b2);
+      Blocks b1;   // the cells in no block that have no hanging node
       for (int64_t c = 0; c < h.ncell; ++c) {
         if (used[size_t(c)]) continue;
         bool hh = false;
         for (int a = 0; a < 27; ++a) hh = hh || slots[size_t(27 * c + a)] < -1;
         (hh ? shang : sreg).push_back(int32_t(c));
+        if (hh) continue;
+        b1.cells.push_back(int32_t(c));
+        b1.slots.insert(b1.slots.end(), slots.begin() + 27 * c, slots.begin() + 27 * (c + 1));
       }
       auto upload_blocks = [&](const Blocks& b, DevBlocks& d, int NC) {
         d.slots = ctx->upload(encode(b.slots));
@@ -456,9 +460,13 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
       };
       upload_blocks(b4, v.blk4, 64);
       upload_blocks(b2, v.blk2, 8);
+      v.blk1.slots = ctx->upload(encode(b1.slots));
+      v.blk1.cells = ctx->upload(b1.cells);
+      v.blk1.n = int64_t(b1.cells.size());
       // face gather: every free face point of a block -> its slot, grouped by node
       {
         std::vector<std::pair<int32_t, int32_t>> nf;   // (node, slot)
+        std::vector<char> is_inner(static_cast<size_t>(h.nnode), 0);
         auto faces = [&](const Blocks& b, int B, int64_t slot0) {
           const int E = 2 * B + 1, P = E * E * E, NC = B * B * B;
           const int64_t nb = int64_t(b.cells.size() / size_t(NC));
@@ -467,28 +475,49 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
               const int px = p % E, py = (p / E) % E, pz = p / (E * E);
               const bool inner = px > 0 && px < E - 1 && py > 0 && py < E - 1 && pz > 0 && pz < E - 1;
               const int32_t nd = b.slots[size_t(k * P + p)];
+              if (inner && nd >= 0) is_inner[size_t(nd)] = 1;
               if (!inner && nd >= 0) nf.emplace_back(nd, int32_t(slot0 + k * P + p));
             }
           return slot0 + nb * P;
         };
         const int64_t s2 = faces(b4, 4, 0);
-        const int64_t ns = faces(b2, 2, s2);
-        std::sort(nf.begin(), nf.end());
-        std::vector<int32_t> fnode, fptr{0}, fent;
-        for (size_t i = 0; i < nf.size(); ++i) {
-          if (i == 0 || nf[i].first != nf[i - 1].first) {
-            if (i) fptr.push_back(int32_t(fent.size()));
-            fnode.push_back(nf[i].first);
+        const int64_t s1 = faces(b2, 2, s2);
+        std::vector<int32_t> fnode, fptr, fent;
+        // node by node (all: every free node but the blocks' inner points)
+        auto group = [&](bool all) {
+          std::sort(nf.begin(), nf.end());
+          fnode.clear();
+          fptr.assign(1, 0);
+          fent.clear();
+          size_t q = 0;
+          auto take = [&](int32_t nd) {
+            fnode.push_back(nd);
+            for (; q < nf.size() && nf[q].first == nd; ++q) fent.push_back(nf[q].second);
+            fptr.push_back(int32_t(fent.size()));
+          };
+          if (all) {
+            for (int64_t i = 0; i < h.nnode; ++i)
+              if (h.ntype[size_t(i)] == NODE_FREE && !is_inner[size_t(i)]) take(int32_t(i));
+          } else {
+            while (q < nf.size()) take(nf[q].first);
           }
-          fent.push_back(nf[i].second);
-        }
-        if (!nf.empty()) fptr.push_back(int32_t(fent.size()));
+        };
+        group(false);
         v.fslot_blk2 = s2;
+        v.fslot_blk1 = s1;
         v.n_face = int64_t(fnode.size());
         if (v.n_face) {
           v.face_node = ctx->upload(fnode);
           v.face_ptr = ctx->upload(fptr);
           v.face_ent = ctx->upload(fent);
+        }
+        const int64_t ns = faces(b1, 1, s1);
+        group(true);
+        v.n_outer = int64_t(fnode.size());
+        if (v.n_outer) {
+          v.outer_node = ctx->upload(fnode);
+          v.outer_ptr = ctx->upload(fptr);
+          v.outer_ent = ctx->upload(fent);
           v.fslot_f = ctx->dalloc<float>(size_t(3 * ns));
           v.fslot_d = ctx->dalloc<double>(size_t(3 * ns));
           if (!v.fslot_f || !v.fslot_d) return ctx->set(MFGMG_ERR_NOMEM, "device allocation failed");
@@ -827,25 +856,16 @@ void smooth_on(mfgmg_ctx* ctx, LevelDev& d, const T* b, T* x, bool x_zero, hipSt
     launch_fused_step<T>(d.v, t, b, minv, dd, x, alpha[3], beta[3], true, s);
     return;
   }
-  // where the operator starts with an output initialisation kernel, each
-  // update prepares t for the next operator call on x instead (after the last
-  // update of a pre-smoothing, for the V-cycle's residual)
-  const bool prep = vmult_has_init(d.v);
-  ChebPrep cp;
-  if (prep) {
-    cp.tn = t;
-    cp.cmask = d.v.cmask;
-  }
+  const uint8_t* mask = step_mask(d.v);
   if (x_zero) {
-    launch_chebx_init0<T>(n, b, minv, dd, x, beta[0], s, cp);
+    launch_chebx_init0<T>(n, b, minv, dd, x, beta[0], s);
   } else {
-    launch_vmult<T>(d.v, x, t, s);
-    launch_chebx_step<T>(n, b, t, minv, dd, x, alpha[0], beta[0], s, cp);
+    launch_vmult_free<T>(d.v, x, t, s);
+    launch_chebx_step<T>(n, b, t, minv, dd, x, alpha[0], beta[0], s, mask);
   }
   for (int k = 1; k < 4; ++k) {
-    if (prep) launch_vmult_prepared<T>(d.v, x, t, s);
-    else launch_vmult<T>(d.v, x, t, s);
-    launch_chebx_step<T>(n, b, t, minv, dd, x, alpha[k], beta[k], s, k < 3 || x_zero ? cp : ChebPrep());
+    launch_vmult_free<T>(d.v, x, t, s);
+    launch_chebx_step<T>(n, b, t, minv, dd, x, alpha[k], beta[k], s, mask);
   }
 }
 
@@ -898,10 +918,8 @@ void vcycle(mfgmg_ctx* ctx, int ell, const T* b, T* x, hipStream_t s) {
   if (smoother_fuses(d.v)) {
     launch_fused_residual<T>(d.v, x, b, t, s);
     rb = t, rt = nullptr;
-  } else if (vmult_has_init(d.v)) {   // the pre-smoothing left t prepared for A x
-    launch_vmult_prepared<T>(d.v, x, t, s);
-  } else {
-    launch_vmult<T>(d.v, x, t, s);
+  } else {   // the restriction reads free dofs only
+    launch_vmult_free<T>(d.v, x, t, s);
   }
   // the smoother's r and d are free here: scratch of the restriction passes
   launch_restrict_level<T>(d.v, c.v, d.R_ptr, d.R_col, d.R_w, rb, rt, bc, static_cast<T*>(d.work[pi][2]),

@@ -104,7 +104,7 @@ struct DevLevel {
   int64_t n_reg_cells = 0;
   // operator partition: blocks of 4^3 and 2^3 same-level cells, and the
   // remaining single cells with and without hanging nodes
-  DevBlocks blk4, blk2;
+  DevBlocks blk4, blk2, blk1;   // blk1: the single_reg cells one by one (velocity tables only)
   const int32_t* single_reg = nullptr;
   int64_t n_single_reg = 0;
   const int32_t* single_hang = nullptr;
@@ -131,6 +131,14 @@ struct DevLevel {
   const int32_t* face_ptr = nullptr;
   const int32_t* face_ent = nullptr;
   int64_t n_face = 0;
+  // the velocity operator's gather: every free node that is no block's inner
+  // point, with its slots over the 4^3, 2^3 and single-cell blocks (none where
+  // only single cells with hanging nodes touch it)
+  int64_t fslot_blk1 = 0;
+  const int32_t* outer_node = nullptr;
+  const int32_t* outer_ptr = nullptr;
+  const int32_t* outer_ent = nullptr;
+  int64_t n_outer = 0;
   // the leaf's pressure mass blocks do the same on their Q1 lattices (one
   // value per lattice point of every block)
   double* pfslot = nullptr;
@@ -170,30 +178,22 @@ void launch_cheb_init(int64_t n, const T* b, const T* t, const T* minv, T* r, T*
 template <typename T>
 void launch_cheb_step(int64_t n, const T* t, const T* minv, T* r, T* d, T* x, double alpha, double beta,
                       hipStream_t s);
-// With p.tn set, the smoother's updates (launch_chebx_*) also prepare the
-// output of the next operator call on a level whose operator starts with an
-// initialisation kernel: tn = (constrained ? the new x : 0); that call is then
-// launch_vmult_prepared.  cmask: the level's constrained-component masks.
-struct ChebPrep {
-  void* tn = nullptr;
-  const uint8_t* cmask = nullptr;
-};
 // the smoother's form (residual b - A x formed each step, r not stored):
 // init0 from x = 0; step: d = alpha d + beta minv (b - t), x += d (alpha = 0:
-// d is not read).  p prepares t for the next operator call on x.
+// d is not read).  cmask (step_mask of the level): t is not read on constrained
+// dofs, whose rows are identities.
 template <typename T>
-void launch_chebx_init0(int64_t n, const T* b, const T* minv, T* d, T* x, double inv_theta, hipStream_t s,
-                        const ChebPrep& p = ChebPrep());
+void launch_chebx_init0(int64_t n, const T* b, const T* minv, T* d, T* x, double inv_theta, hipStream_t s);
 template <typename T>
 void launch_chebx_step(int64_t n, const T* b, const T* t, const T* minv, T* d, T* x, double alpha, double beta,
-                       hipStream_t s, const ChebPrep& p = ChebPrep());
-// true when launch_vmult on L starts with an output initialisation kernel
-// (the general levels but those run as a grid)
-bool vmult_has_init(const DevLevel& L);
-// y = A x like launch_vmult (init), for a y already holding x on the
-// constrained dofs and 0 elsewhere (the initialisation kernel is skipped)
+                       hipStream_t s, const uint8_t* cmask);
+// constrained-component masks of the levels whose operator writes its identity
+// rows in a pass of its own (general levels), else null
+const uint8_t* step_mask(const DevLevel& L);
+// y = A x like launch_vmult (init), leaving y undefined on constrained dofs
+// where the level has a step_mask
 template <typename T>
-void launch_vmult_prepared(const DevLevel& L, const T* x, T* y, hipStream_t s);
+void launch_vmult_free(const DevLevel& L, const T* x, T* y, hipStream_t s);
 
 // Uniform levels and grid levels up to 32^3 cells: the smoother's update and the residual
 // formed inside the operator's kernel.  y must be neither x nor b.

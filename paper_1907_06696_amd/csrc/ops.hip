@@ -61,19 +61,9 @@ struct UniformCell {
 };
 
 // ------------------------------------------------------------- vmult
-template <typename T>
-__global__ __launch_bounds__(256) void k_init_out_general(int64_t nn, const uint8_t* __restrict__ cmask,
-                                                          const T* __restrict__ x, T* __restrict__ y) {
-  for (int64_t v = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; v < nn; v += int64_t(gridDim.x) * blockDim.x) {
-    const unsigned b = cmask[v];
-    y[3 * v] = (b & 1) ? x[3 * v] : T(0);
-    y[3 * v + 1] = (b & 2) ? x[3 * v + 1] : T(0);
-    y[3 * v + 2] = (b & 4) ? x[3 * v + 2] : T(0);
-  }
-}
-
-// y(node) += the face slots of the node (one thread per node, 2-8 slots)
-template <typename T>
+// y(node) = (SET) or += the face slots of the node (one thread per node, up to
+// 8 slots; none where only single cells with hanging nodes touch it)
+template <typename T, bool SET>
 __global__ __launch_bounds__(kBlock) void k_face_gather(int64_t nf, const int32_t* __restrict__ node,
                                                         const int32_t* __restrict__ ptr,
                                                         const int32_t* __restrict__ ent,
@@ -85,8 +75,17 @@ __global__ __launch_bounds__(kBlock) void k_face_gather(int64_t nf, const int32_
       a0 += fs[0], a1 += fs[1], a2 += fs[2];
     }
     T* yp = y + 3 * int64_t(node[i]);
-    yp[0] += a0, yp[1] += a1, yp[2] += a2;
+    if constexpr (SET) yp[0] = a0, yp[1] = a1, yp[2] = a2;
+    else yp[0] += a0, yp[1] += a1, yp[2] += a2;
   }
+}
+
+// identity rows: y = x on the listed constrained dofs
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_identity(int64_t n, const int64_t* __restrict__ dofs,
+                                                     const T* __restrict__ x, T* __restrict__ y) {
+  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x)
+    y[dofs[i]] = x[dofs[i]];
 }
 
 // pressure version (one value per slot); returns when the gate is set, as the
@@ -115,10 +114,10 @@ double* face_slots<double>(const DevLevel& L) {
   return L.fslot_d;
 }
 
-// The single cells of a non-uniform level (those in no block): the cell
-// operator with three threads per cell, one velocity component each (a wave
+// The single cells with hanging nodes of a non-uniform level (those in no
+// block): the cell operator with three threads per cell, one velocity component each (a wave
 // per component), hanging nodes resolved through the
-// level's constraint rows (HANG).  A thread gathers,
+// level's constraint rows.  A thread gathers,
 // transforms and scatters its component's 27 values and computes its
 // component's rows of the cell operator from the modes of all three
 // components, exchanged through LDS.  The single cells are few, so the kernel
@@ -150,7 +149,7 @@ __device__ __forceinline__ void scatter1(int32_t s, int comp, T v, T* __restrict
       if (!cm || !((cm[hm[q]] >> comp) & 1)) atomic_add(&y[3 * int64_t(hm[q]) + comp], hw[q] * v);
   }
 }
-template <typename T, bool HANG>
+template <typename T>
 __global__ __launch_bounds__(192) void k_vmult_general3(const int32_t* __restrict__ cells, int64_t ncells,
                                                         const int32_t* __restrict__ slots,
                                                         const int8_t* __restrict__ clev, const T* __restrict__ mu,
@@ -169,10 +168,7 @@ __global__ __launch_bounds__(192) void k_vmult_general3(const int32_t* __restric
 #pragma unroll
   for (int a = 0; a < 27; ++a) {
     sl[a] = slots[27 * c + a];
-    if constexpr (HANG)
-      w[a] = gather1<T>(sl[a], comp, x, hptr, hm, hw, cm);
-    else
-      w[a] = sl[a] >= 0 && !slot_fixed(sl[a], comp) ? x[3 * int64_t(slot_node(sl[a])) + comp] : T(0);
+    w[a] = gather1<T>(sl[a], comp, x, hptr, hm, hw, cm);
   }
   const T mu_h = mu[c] * T(ldexp(1.0, -int(clev[c])));
   cellop::modes_all(w);
@@ -187,17 +183,13 @@ __global__ __launch_bounds__(192) void k_vmult_general3(const int32_t* __restric
   for (int a = 0; a < 27; ++a) w[a] *= mu_h;
   if (!live) return;
 #pragma unroll
-  for (int a = 0; a < 27; ++a) {
-    if constexpr (HANG)
-      scatter1<T>(sl[a], comp, w[a], y, hptr, hm, hw, cm);
-    else if (sl[a] >= 0 && !slot_fixed(sl[a], comp))
-      atomic_add(&y[3 * int64_t(slot_node(sl[a])) + comp], w[a]);
-  }
+  for (int a = 0; a < 27; ++a) scatter1<T>(sl[a], comp, w[a], y, hptr, hm, hw, cm);
 }
 
 // Blocks of B x B x B same-level cells on a non-uniform level (complete
 // sibling groups of the level mesh: the 8 children, or the 64 grandchildren,
-// of one cell).  One wave per workgroup treats 64 / B^3 blocks, one lane per
+// of one cell; B = 1: the remaining cells without hanging nodes, which took 30
+// us of scattered loads and device-scope atomics per call).  One wave per workgroup treats 64 / B^3 blocks, one lane per
 // cell.  As in the brick kernel, each block's (2B+1)^3 node box is staged in
 // LDS, the cells gather from LDS, and their results are accumulated in LDS
 // class by class (local node a in {0,1} | {2} per axis: within a class no
@@ -289,29 +281,46 @@ __global__ __launch_bounds__(64) void k_vmult_blocks(DevBlocks blk, const int8_t
   // whose FP32 form is slow here (leaf of the adaptive 32^3 + 2 workload: 144
   // -> 125 us per call); FP64: one lane per entry with LDS atomics (the
   // grouped form: 198 -> 225 us)
-  if constexpr (sizeof(T) == 8) {
+  // Entries are loaded eight at a time before any is used: one by one, each
+  // waits for its own load, and a wave of eight 2^3 blocks with a few thousand
+  // entries was a 30 us chain of them.
+  constexpr int kU = 8;
+  if constexpr (B > 1 && sizeof(T) == 8) {
     const int h0 = blk.hoff[blk0], h1 = blk.hoff[blk0 + nb];
-    for (int e = h0 + lane; e < h1; e += 64) {
-      const int32_t en = blk.hent[e];
-      const int p = en & 1023, pm = (en >> 10) & 1023, bl = en >> 20;
-      const T w = hw[e];
-      const int o = lds_of(bl, p), om = lds_of(bl, pm);
+    for (int e0 = h0 + lane; e0 < h1; e0 += 64 * kU) {
+      int32_t en[kU];
+      T w[kU];
 #pragma unroll
-      for (int q = 0; q < 3; ++q) atomicAdd(&buf[o + q * P], w * buf[om + q * P]);
+      for (int u = 0; u < kU; ++u) {
+        const int e = min(e0 + 64 * u, h1 - 1);
+        en[u] = blk.hent[e], w[u] = hw[e];
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        if (e0 + 64 * u >= h1) break;
+        const int o = lds_of(en[u] >> 20, en[u] & 1023), om = lds_of(en[u] >> 20, (en[u] >> 10) & 1023);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) atomicAdd(&buf[o + q * P], w[u] * buf[om + q * P]);
+      }
     }
-  } else {
+  } else if constexpr (B > 1) {
     const int k0 = blk.g1off[blockIdx.x], k1 = blk.g1off[blockIdx.x + 1] - 1;
     for (int k = k0 + lane; k < k1; k += 64) {
-      const int e0 = blk.g1[k], e1 = blk.g1[k + 1];
+      const int g0 = blk.g1[k], g1 = blk.g1[k + 1];
       T a0 = T(0), a1 = T(0), a2 = T(0);
       int o = 0;
-      for (int e = e0; e < e1; ++e) {
-        const int32_t en = blk.hent[e];
-        const int p = en & 1023, pm = (en >> 10) & 1023, bl = en >> 20;
-        const T w = hw[e];
-        const int om = lds_of(bl, pm);
-        o = lds_of(bl, p);
-        a0 += w * buf[om], a1 += w * buf[om + P], a2 += w * buf[om + 2 * P];
+      for (int e0 = g0; e0 < g1; e0 += kU) {
+        int32_t en[kU];
+        T w[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) en[u] = blk.hent[min(e0 + u, g1 - 1)], w[u] = hw[min(e0 + u, g1 - 1)];
+        o = lds_of(en[0] >> 20, en[0] & 1023);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          if (e0 + u >= g1) break;
+          const int om = lds_of(en[u] >> 20, (en[u] >> 10) & 1023);
+          a0 += w[u] * buf[om], a1 += w[u] * buf[om + P], a2 += w[u] * buf[om + 2 * P];
+        }
       }
       buf[o] = a0, buf[o + P] = a1, buf[o + 2 * P] = a2;
     }
@@ -332,7 +341,8 @@ __global__ __launch_bounds__(64) void k_vmult_blocks(DevBlocks blk, const int8_t
         for (int q = 0; q < 3; ++q) U[q][xx + 3 * yy + 9 * z] = buf[off + q * P];
       }
   __syncthreads();
-  for (int e = lane; e < NB * W; e += 64) buf[e] = T(0);
+  if constexpr (B > 1)
+    for (int e = lane; e < NB * W; e += 64) buf[e] = T(0);
   T coef = T(0);
   if (bl < nb) {
     const int32_t c = blk.cells[(blk0 + bl) * NC + lc];
@@ -340,8 +350,16 @@ __global__ __launch_bounds__(64) void k_vmult_blocks(DevBlocks blk, const int8_t
   }
   cellop::apply_cell(U);
   __syncthreads();
+  if constexpr (B == 1) {   // a single cell's points are its own
 #pragma unroll
-  for (int cls = 0; cls < 8; ++cls) {
+    for (int a = 0; a < 27; ++a) {
+      const int off = base + bsplit<B>(a % 3) + E * bsplit<B>(a / 3 % 3) + E * E * bsplit<B>(a / 9);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) buf[off + q * P] = coef * U[q][a];
+    }
+  }
+#pragma unroll
+  for (int cls = 0; cls < (B == 1 ? 0 : 8); ++cls) {
     const int ac = cls & 1, bc = (cls >> 1) & 1, zc = cls >> 2;
 #pragma unroll
     for (int z = zc ? 2 : 0; z < (zc ? 3 : 2); ++z)
@@ -359,30 +377,43 @@ __global__ __launch_bounds__(64) void k_vmult_blocks(DevBlocks blk, const int8_t
   // hanging entries themselves are not read again): FP64 one lane per entry
   // with LDS atomics, FP32 one lane per master over the entries sorted by
   // master
-  if constexpr (sizeof(T) == 8) {
+  if constexpr (B > 1 && sizeof(T) == 8) {
     const int h0 = blk.hoff[blk0], h1 = blk.hoff[blk0 + nb];
-    for (int e = h0 + lane; e < h1; e += 64) {
-      const int32_t en = blk.hent[e];
-      const int p = en & 1023, pm = (en >> 10) & 1023, bl2 = en >> 20;
-      const T w = hw[e];
-      const int o = lds_of(bl2, p), om = lds_of(bl2, pm);
+    for (int e0 = h0 + lane; e0 < h1; e0 += 64 * kU) {
+      int32_t en[kU];
+      T w[kU];
 #pragma unroll
-      for (int q = 0; q < 3; ++q) atomicAdd(&buf[om + q * P], w * buf[o + q * P]);
+      for (int u = 0; u < kU; ++u) {
+        const int e = min(e0 + 64 * u, h1 - 1);
+        en[u] = blk.hent[e], w[u] = hw[e];
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        if (e0 + 64 * u >= h1) break;
+        const int o = lds_of(en[u] >> 20, en[u] & 1023), om = lds_of(en[u] >> 20, (en[u] >> 10) & 1023);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) atomicAdd(&buf[om + q * P], w[u] * buf[o + q * P]);
+      }
     }
-  } else {
+  } else if constexpr (B > 1) {
     const T* __restrict__ hw2 = blk_hw2<T>(blk);
     const int k0 = blk.g2off[blockIdx.x], k1 = blk.g2off[blockIdx.x + 1] - 1;
     for (int k = k0 + lane; k < k1; k += 64) {
-      const int e0 = blk.g2[k], e1 = blk.g2[k + 1];
+      const int g0 = blk.g2[k], g1 = blk.g2[k + 1];
       T a0 = T(0), a1 = T(0), a2 = T(0);
       int om = 0;
-      for (int e = e0; e < e1; ++e) {
-        const int32_t en = blk.hent2[e];
-        const int p = en & 1023, pm = (en >> 10) & 1023, bl2 = en >> 20;
-        const T w = hw2[e];
-        const int o = lds_of(bl2, p);
-        om = lds_of(bl2, pm);
-        a0 += w * buf[o], a1 += w * buf[o + P], a2 += w * buf[o + 2 * P];
+      for (int e0 = g0; e0 < g1; e0 += kU) {
+        int32_t en[kU];
+        T w[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) en[u] = blk.hent2[min(e0 + u, g1 - 1)], w[u] = hw2[min(e0 + u, g1 - 1)];
+        om = lds_of(en[0] >> 20, (en[0] >> 10) & 1023);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          if (e0 + u >= g1) break;
+          const int o = lds_of(en[u] >> 20, en[u] & 1023);
+          a0 += w[u] * buf[o], a1 += w[u] * buf[o + P], a2 += w[u] * buf[o + 2 * P];
+        }
       }
       buf[om] += a0, buf[om + P] += a1, buf[om + 2 * P] += a2;
     }
@@ -541,24 +572,6 @@ __global__ void k_invert_diag_general(int64_t nn, const uint8_t* __restrict__ cm
 }
 
 // ------------------------------------------------------------- Chebyshev
-// The smoother's Chebyshev updates (k_chebx_*) can also prepare the output of
-// the next operator call on general levels, whose operator otherwise starts
-// with an initialisation kernel (k_init_out_general): tn = the new x on
-// constrained dofs (their bits of cmask), 0 elsewhere.  tn may be t itself
-// (each entry is read before it is written, by the same thread; t and tn are
-// therefore not restrict).
-template <typename T>
-struct OutPrep {
-  T* tn;
-  const uint8_t* cmask;
-};
-template <typename T>
-__device__ __forceinline__ void out_prep(const OutPrep<T>& o, int64_t i, T xi) {
-  if (!o.tn) return;
-  const int64_t v = i / 3;
-  o.tn[i] = ((o.cmask[v] >> (i - 3 * v)) & 1) ? xi : T(0);
-}
-
 template <typename T>
 __global__ void k_cheb_init0(int64_t n, const T* __restrict__ b, const T* __restrict__ minv, T* __restrict__ r,
                              T* __restrict__ d, T* __restrict__ x, T it) {
@@ -608,30 +621,35 @@ __global__ void k_cheb_step(int64_t n, const T* __restrict__ t, const T* __restr
 // exact arithmetic), so r is never stored and the operator is applied to x.
 // x0 = 0: d = (1/theta) M b, x = d; first step from a given x: t = A x,
 // d = (1/theta) M (b - t), x += d; later steps: d = alpha d + beta M (b - t),
-// x += d.  Each prepares t for the next operator call on x (out_prep).
+// x += d.  cmask (general levels, else null): the constrained components of
+// each node, whose t is not read: there A x = x (identity rows).
 template <typename T>
 __global__ void k_chebx_init0(int64_t n, const T* __restrict__ b, const T* __restrict__ minv, T* __restrict__ d,
-                              T* __restrict__ x, T it, OutPrep<T> o) {
+                              T* __restrict__ x, T it) {
   for (int64_t i = brick::xcd_order(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x; i < n;
        i += int64_t(gridDim.x) * blockDim.x) {
     const T di = minv[i] * b[i] * it;
     d[i] = di;
     x[i] = di;
-    out_prep(o, i, di);
   }
 }
 template <typename T>
-__global__ void k_chebx_step(int64_t n, const T* __restrict__ b, const T* t, const T* __restrict__ minv,
-                             T* __restrict__ d, T* __restrict__ x, T alpha, T beta, OutPrep<T> o) {
+__global__ void k_chebx_step(int64_t n, const T* __restrict__ b, const T* __restrict__ t, const T* __restrict__ minv,
+                             T* __restrict__ d, T* __restrict__ x, T alpha, T beta, const uint8_t* __restrict__ cmask) {
   // alpha = 0: the first step from a given x (d is not read)
   for (int64_t i = brick::xcd_order(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x; i < n;
        i += int64_t(gridDim.x) * blockDim.x) {
-    const T ri = b[i] - t[i];
+    const T x0 = x[i];
+    T ti = t[i];
+    if (cmask) {
+      const int64_t v = i / 3;
+      if ((cmask[v] >> (i - 3 * v)) & 1) ti = x0;
+    }
+    const T ri = b[i] - ti;
     const T di = (alpha != T(0) ? alpha * d[i] : T(0)) + beta * minv[i] * ri;
-    const T xi = x[i] + di;
+    const T xi = x0 + di;
     d[i] = di;
     x[i] = xi;
-    out_prep(o, i, xi);
   }
 }
 
@@ -2473,7 +2491,7 @@ void launch_owner(const DevLevel& L, const T* x, const T* b, const T* minv, T* d
 }
 
 template <typename T>
-void vmult_impl(const DevLevel& L, const T* x, T* y, hipStream_t s, bool init, bool prepared) {
+void vmult_impl(const DevLevel& L, const T* x, T* y, hipStream_t s, bool init, bool free_only) {
   if (L.uniform) {
     const int64_t n = L.n_edge;
     T* halo = brick_halo<T>(L);
@@ -2492,31 +2510,37 @@ void vmult_impl(const DevLevel& L, const T* x, T* y, hipStream_t s, bool init, b
     else launch_owner<owner::Op::Add, T>(L, x, nullptr, nullptr, nullptr, y, 0.0, 0.0, 0.0, s);
     return;
   }
-  if (L.q3) {   // owner-computes: no initialisation kernel (vmult_has_init is false)
+  if (L.q3) {   // owner-computes: no initialisation kernel 
     launch_vmult_q3<T>(L, x, y, !init, s);
     return;
   }
-  if (init && !prepared) k_init_out_general<T><<<grid_for(L.nnode), kBlock, 0, s>>>(L.nnode, L.cmask, x, y);
+  // the blocks store their inner points and leave the others in slots, which
+  // the gather sums into every other free node; cells with hanging nodes
+  // outside a block add to those sums; identity rows last
   T* fs = face_slots<T>(L);
-  if (L.blk4.n) {
-    if (init) k_vmult_blocks<T, 4, false><<<unsigned(L.blk4.n), 64, 0, s>>>(L.blk4, L.clev, mu_of<T>(L), x, y, fs);
-    else k_vmult_blocks<T, 4, true><<<unsigned(L.blk4.n), 64, 0, s>>>(L.blk4, L.clev, mu_of<T>(L), x, y, fs);
+  const unsigned g2 = unsigned((L.blk2.n + 7) / 8), g1 = unsigned((L.blk1.n + 63) / 64);
+  T *fs2 = fs + 3 * L.fslot_blk2, *fs1 = fs + 3 * L.fslot_blk1;
+  if (init) {
+    if (L.blk4.n) k_vmult_blocks<T, 4, false><<<unsigned(L.blk4.n), 64, 0, s>>>(L.blk4, L.clev, mu_of<T>(L), x, y, fs);
+    if (L.blk2.n) k_vmult_blocks<T, 2, false><<<g2, 64, 0, s>>>(L.blk2, L.clev, mu_of<T>(L), x, y, fs2);
+    if (L.blk1.n) k_vmult_blocks<T, 1, false><<<g1, 64, 0, s>>>(L.blk1, L.clev, mu_of<T>(L), x, y, fs1);
+    if (L.n_outer)
+      k_face_gather<T, true><<<grid_for(L.n_outer), kBlock, 0, s>>>(L.n_outer, L.outer_node, L.outer_ptr, L.outer_ent,
+                                                                   fs, y);
+  } else {
+    if (L.blk4.n) k_vmult_blocks<T, 4, true><<<unsigned(L.blk4.n), 64, 0, s>>>(L.blk4, L.clev, mu_of<T>(L), x, y, fs);
+    if (L.blk2.n) k_vmult_blocks<T, 2, true><<<g2, 64, 0, s>>>(L.blk2, L.clev, mu_of<T>(L), x, y, fs2);
+    if (L.blk1.n) k_vmult_blocks<T, 1, true><<<g1, 64, 0, s>>>(L.blk1, L.clev, mu_of<T>(L), x, y, fs1);
+    if (L.n_outer)
+      k_face_gather<T, false><<<grid_for(L.n_outer), kBlock, 0, s>>>(L.n_outer, L.outer_node, L.outer_ptr, L.outer_ent,
+                                                                    fs, y);
   }
-  if (L.blk2.n) {
-    const unsigned g = unsigned((L.blk2.n + 7) / 8);
-    T* fs2 = fs + 3 * L.fslot_blk2;
-    if (init) k_vmult_blocks<T, 2, false><<<g, 64, 0, s>>>(L.blk2, L.clev, mu_of<T>(L), x, y, fs2);
-    else k_vmult_blocks<T, 2, true><<<g, 64, 0, s>>>(L.blk2, L.clev, mu_of<T>(L), x, y, fs2);
-  }
-  if (L.n_single_reg)
-    k_vmult_general3<T, false><<<unsigned((L.n_single_reg + 63) / 64), 192, 0, s>>>(
-        L.single_reg, L.n_single_reg, L.slots, L.clev, mu_of<T>(L), nullptr, nullptr, nullptr, nullptr, x, y);
   if (L.n_single_hang)
-    k_vmult_general3<T, true><<<unsigned((L.n_single_hang + 63) / 64), 192, 0, s>>>(
+    k_vmult_general3<T><<<unsigned((L.n_single_hang + 63) / 64), 192, 0, s>>>(
         L.single_hang, L.n_single_hang, L.slots, L.clev, mu_of<T>(L), L.hptr, L.hmaster, hw_of<T>(L),
         L.noflux ? L.cmask : nullptr, x, y);
-  if (L.n_face)
-    k_face_gather<T><<<grid_for(L.n_face), kBlock, 0, s>>>(L.n_face, L.face_node, L.face_ptr, L.face_ent, fs, y);
+  if (init && !free_only && L.n_cons)
+    k_identity<T><<<grid_for(L.n_cons), kBlock, 0, s>>>(L.n_cons, L.cons_dofs, x, y);
 }
 }  // namespace
 template <typename T>
@@ -2524,10 +2548,10 @@ void launch_vmult(const DevLevel& L, const T* x, T* y, hipStream_t s, bool init)
   vmult_impl<T>(L, x, y, s, init, false);
 }
 template <typename T>
-void launch_vmult_prepared(const DevLevel& L, const T* x, T* y, hipStream_t s) {
+void launch_vmult_free(const DevLevel& L, const T* x, T* y, hipStream_t s) {
   vmult_impl<T>(L, x, y, s, true, true);
 }
-bool vmult_has_init(const DevLevel& L) { return !L.q3 && !L.uniform && !L.grid_edge; }
+const uint8_t* step_mask(const DevLevel& L) { return !L.q3 && !L.uniform && !L.grid_edge ? L.cmask : nullptr; }
 
 bool smoother_fuses(const DevLevel& L) { return L.grid_edge || (L.uniform && L.n_edge <= kFusedMaxEdge); }
 template <typename T>
@@ -2555,8 +2579,8 @@ void launch_fused_residual(const DevLevel& L, const T* x, const T* b, T* y, hipS
 MFGMG_FUSED(float)
 MFGMG_FUSED(double)
 #undef MFGMG_FUSED
-template void launch_vmult_prepared<float>(const DevLevel&, const float*, float*, hipStream_t);
-template void launch_vmult_prepared<double>(const DevLevel&, const double*, double*, hipStream_t);
+template void launch_vmult_free<float>(const DevLevel&, const float*, float*, hipStream_t);
+template void launch_vmult_free<double>(const DevLevel&, const double*, double*, hipStream_t);
 template void launch_vmult<float>(const DevLevel&, const float*, float*, hipStream_t, bool);
 template void launch_vmult<double>(const DevLevel&, const double*, double*, hipStream_t, bool);
 
@@ -2598,24 +2622,20 @@ void launch_cheb_step(int64_t n, const T* t, const T* minv, T* r, T* d, T* x, do
   k_cheb_step<T><<<grid_for(n), kBlock, 0, s>>>(n, t, minv, r, d, x, T(alpha), T(beta));
 }
 template <typename T>
-void launch_chebx_init0(int64_t n, const T* b, const T* minv, T* d, T* x, double it, hipStream_t s,
-                        const ChebPrep& p) {
-  k_chebx_init0<T><<<grid_for(n), kBlock, 0, s>>>(n, b, minv, d, x, T(it), OutPrep<T>{static_cast<T*>(p.tn), p.cmask});
+void launch_chebx_init0(int64_t n, const T* b, const T* minv, T* d, T* x, double it, hipStream_t s) {
+  k_chebx_init0<T><<<grid_for(n), kBlock, 0, s>>>(n, b, minv, d, x, T(it));
 }
 template <typename T>
 void launch_chebx_step(int64_t n, const T* b, const T* t, const T* minv, T* d, T* x, double alpha, double beta,
-                       hipStream_t s, const ChebPrep& p) {
-  k_chebx_step<T><<<grid_for(n), kBlock, 0, s>>>(n, b, t, minv, d, x, T(alpha), T(beta),
-                                               OutPrep<T>{static_cast<T*>(p.tn), p.cmask});
+                       hipStream_t s, const uint8_t* cmask) {
+  k_chebx_step<T><<<grid_for(n), kBlock, 0, s>>>(n, b, t, minv, d, x, T(alpha), T(beta), cmask);
 }
-template void launch_chebx_init0<float>(int64_t, const float*, const float*, float*, float*, double, hipStream_t,
-                                        const ChebPrep&);
-template void launch_chebx_init0<double>(int64_t, const double*, const double*, double*, double*, double, hipStream_t,
-                                         const ChebPrep&);
+template void launch_chebx_init0<float>(int64_t, const float*, const float*, float*, float*, double, hipStream_t);
+template void launch_chebx_init0<double>(int64_t, const double*, const double*, double*, double*, double, hipStream_t);
 template void launch_chebx_step<float>(int64_t, const float*, const float*, const float*, float*, float*, double,
-                                       double, hipStream_t, const ChebPrep&);
+                                       double, hipStream_t, const uint8_t*);
 template void launch_chebx_step<double>(int64_t, const double*, const double*, const double*, double*, double*,
-                                        double, double, hipStream_t, const ChebPrep&);
+                                        double, double, hipStream_t, const uint8_t*);
 #define MFGMG_INST_CHEB(T)                                                                                   \
   template void launch_cheb_init0<T>(int64_t, const T*, const T*, T*, T*, T*, double, hipStream_t);          \
   template void launch_cheb_init<T>(int64_t, const T*, const T*, const T*, T*, T*, T*, double, hipStream_t); \
@@ -2850,8 +2870,8 @@ void launch_grad_add(const DevLevel& L, const DevPressure& P, const double* p, d
         k_grad_add<<<unsigned((lst.second + kCellBlock - 1) / kCellBlock), kCellBlock, 0, s>>>(
             L, P, lst.first, lst.second, p, uo);
     if (L.n_face)
-      k_face_gather<double><<<grid_for(L.n_face), kBlock, 0, s>>>(L.n_face, L.face_node, L.face_ptr, L.face_ent, fs,
-                                                                   uo);
+      k_face_gather<double, false>
+          <<<grid_for(L.n_face), kBlock, 0, s>>>(L.n_face, L.face_node, L.face_ptr, L.face_ent, fs, uo);
   } else {
     k_grad_add<<<unsigned((L.ncell + kCellBlock - 1) / kCellBlock), kCellBlock, 0, s>>>(L, P, nullptr, L.ncell, p,
                                                                                          uo);
