@@ -301,6 +301,13 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
         std::vector<int32_t> pslots, phoff{0}, phent;   // leaf: Q1 pressure lattice
         std::vector<double> phw;
       };
+      // position of a block's lattice point in its tables, the block kernels'
+      // LDS order: per axis the even points, then the odd ones
+      auto place = [](int B, int px, int py, int pz) {
+        const int E = 2 * B + 1;
+        auto split = [B](int l) { return (l & 1) ? B + 1 + l / 2 : l / 2; };
+        return split(px) + E * (split(py) + E * split(pz));
+      };
       auto make_blocks = [&](int B, Blocks& out) {
         const int E = 2 * B + 1, NC = B * B * B, P = E * E * E, NB = 64 / NC;
         std::vector<int32_t> cs(static_cast<size_t>(NC)), bs(static_cast<size_t>(P));
@@ -321,7 +328,7 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
           for (int q = 0; q < NC; ++q) {
             const int qa = q % B, qb = (q / B) % B, qc = q / (B * B);
             for (int a = 0; a < 27; ++a) {
-              const int p = (2 * qa + a % 3) + E * ((2 * qb + (a / 3) % 3) + E * (2 * qc + a / 9));
+              const int p = place(B, 2 * qa + a % 3, 2 * qb + (a / 3) % 3, 2 * qc + a / 9);
               bs[size_t(p)] = slots[size_t(27 * int64_t(cs[size_t(q)]) + a)];
             }
           }
@@ -331,7 +338,7 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
           ent.clear();
           wt.clear();
           const int32_t bl = int32_t((out.cells.size() / size_t(NC)) % size_t(NB));
-          for (int p = 0; p < P && ok; ++p) {
+          for (int p = 0; p < P && ok; ++p) {   // (in table order: entries of a point are consecutive)
             if (bs[size_t(p)] >= -1) continue;
             const int64_t hr = -int64_t(bs[size_t(p)]) - 2;
             for (int64_t q = h.hang.ptr[size_t(hr)]; q < h.hang.ptr[size_t(hr + 1)] && ok; ++q) {
@@ -398,6 +405,7 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
       make_blocks(4, b4);
       make_blocks(2, b2);
       Blocks b1;   // the cells in no block that have no hanging node
+      std::vector<int32_t> cs1(27);
       for (int64_t c = 0; c < h.ncell; ++c) {
         if (used[size_t(c)]) continue;
         bool hh = false;
@@ -405,7 +413,8 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
         (hh ? shang : sreg).push_back(int32_t(c));
         if (hh) continue;
         b1.cells.push_back(int32_t(c));
-        b1.slots.insert(b1.slots.end(), slots.begin() + 27 * c, slots.begin() + 27 * (c + 1));
+        for (int a = 0; a < 27; ++a) cs1[size_t(place(1, a % 3, a / 3 % 3, a / 9))] = slots[size_t(27 * c + a)];
+        b1.slots.insert(b1.slots.end(), cs1.begin(), cs1.end());
       }
       auto upload_blocks = [&](const Blocks& b, DevBlocks& d, int NC) {
         d.slots = ctx->upload(encode(b.slots));
@@ -472,8 +481,8 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
           const int64_t nb = int64_t(b.cells.size() / size_t(NC));
           for (int64_t k = 0; k < nb; ++k)
             for (int p = 0; p < P; ++p) {
-              const int px = p % E, py = (p / E) % E, pz = p / (E * E);
-              const bool inner = px > 0 && px < E - 1 && py > 0 && py < E - 1 && pz > 0 && pz < E - 1;
+              auto face = [B](int s) { return s == 0 || s == B; };   // split order: 0 and 2B
+              const bool inner = !face(p % E) && !face(p / E % E) && !face(p / (E * E));
               const int32_t nd = b.slots[size_t(k * P + p)];
               if (inner && nd >= 0) is_inner[size_t(nd)] = 1;
               if (!inner && nd >= 0) nf.emplace_back(nd, int32_t(slot0 + k * P + p));

@@ -19,9 +19,10 @@ __host__ __device__ __forceinline__ int32_t slot_node(int32_t s) { return s & kS
 __host__ __device__ __forceinline__ bool slot_fixed(int32_t s, int c) { return (s >> (kSlotFixShift + c)) & 1; }
 
 // Blocks of B^3 same-level cells of a non-uniform level: node-box slots
-// [(2B+1)^3] per block (x fastest; node >= 0 free, -1 Dirichlet, -2
+// [(2B+1)^3] per block (x fastest, on each axis the even lattice points before
+// the odd ones: the kernels' LDS order; node >= 0 free, -1 Dirichlet, -2
 // hanging), cell indices [B^3], and the hanging points' masters as lattice
-// points of the same block: entries hoff[b] .. hoff[b+1] of block b pack
+// points (in that order) of the same block: entries hoff[b] .. hoff[b+1] of block b pack
 // (point | master << 10 | (b mod blocks-per-workgroup) << 20) with weight hw.
 struct DevBlocks {
   const int32_t* slots = nullptr;

@@ -70,11 +70,22 @@ __global__ __launch_bounds__(kBlock) void k_face_gather(int64_t nf, const int32_
                                                         const T* __restrict__ fslot, T* __restrict__ y) {
   for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < nf; i += int64_t(gridDim.x) * blockDim.x) {
     T a0 = T(0), a1 = T(0), a2 = T(0);
-    for (int32_t e = ptr[i]; e < ptr[i + 1]; ++e) {
-      const T* fs = fslot + 3 * int64_t(ent[e]);
-      a0 += fs[0], a1 += fs[1], a2 += fs[2];
-    }
     T* yp = y + 3 * int64_t(node[i]);
+    const int32_t e1 = ptr[i + 1];
+    // four slots at a time, their loads issued together: the kernel is a
+    // chain of dependent loads (one at a time 37 us, so 29 us on the leaf of the
+    // adaptive 32^3 + 2 workload, FP32)
+    for (int32_t e = ptr[i]; e < e1; e += 4) {
+      T v[4][3];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const T* fs = fslot + 3 * int64_t(ent[min(e + u, e1 - 1)]);
+        v[u][0] = fs[0], v[u][1] = fs[1], v[u][2] = fs[2];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (e + u < e1) a0 += v[u][0], a1 += v[u][1], a2 += v[u][2];
+    }
     if constexpr (SET) yp[0] = a0, yp[1] = a1, yp[2] = a2;
     else yp[0] += a0, yp[1] += a1, yp[2] += a2;
   }
@@ -189,21 +200,47 @@ __global__ __launch_bounds__(192) void k_vmult_general3(const int32_t* __restric
 // Blocks of B x B x B same-level cells on a non-uniform level (complete
 // sibling groups of the level mesh: the 8 children, or the 64 grandchildren,
 // of one cell; B = 1: the remaining cells without hanging nodes, which took 30
-// us of scattered loads and device-scope atomics per call).  One wave per workgroup treats 64 / B^3 blocks, one lane per
-// cell.  As in the brick kernel, each block's (2B+1)^3 node box is staged in
+// us of scattered loads and device-scope atomics per call).  One wave per
+// workgroup treats 64 / B^3 blocks, one lane per cell.  As in the brick kernel, each block's (2B+1)^3 node box is staged in
 // LDS, the cells gather from LDS, and their results are accumulated in LDS
 // class by class (local node a in {0,1} | {2} per axis: within a class no
 // two cells of a block share a node).  Hanging points are resolved inside
 // the box: their masters are lattice points of the same block, so the
 // gather interpolates them from the staged masters and the write-back first
 // distributes their accumulated values onto the masters (FP64: LDS atomics;
-// FP32: one lane per hanging point, then one per master).  Nodes strictly inside a block belong to its cells alone and are
-// stored; the values of its free face nodes go to the block's face slots
+// FP32: one lane per hanging point, then one per master).  Nodes strictly
+// inside a block belong to its cells alone and are stored; the values of its free face nodes go to the block's face slots
 // and k_face_gather adds each node's slots into y.  LDS layout per block and
 // component: every axis split into even then odd lattice points.
+// Bound by latency: a wave's life is four dependent phases (tables, staging,
+// cells, write-back) and LDS admits four waves per SIMD; it moves 158 MB in 81
+// us on the leaf of the adaptive 32^3 + 2 workload (4^3 blocks, FP32), where
+// half of its operations were index arithmetic before the tables came in LDS
+// order (95 us; 2^3 blocks 44 -> 34 us).
 template <int B>
 __device__ __forceinline__ int bsplit(int l) {
   return (l & 1) ? (B + 1) + (l >> 1) : (l >> 1);
+}
+// The host stores each block's points in this order, so a table position is an
+// LDS position.  Which positions lie strictly inside the block: bit
+// `lane` of word k for position (lane + 64 k) of a wave's blocks.
+template <int B>
+struct InnerPoints {
+  static constexpr int E = 2 * B + 1, P = E * E * E, NB = 64 / (B * B * B), K = (NB * P + 63) / 64;
+  uint64_t word[K];
+  static constexpr bool on_face(int s) { return s == 0 || s == B; }   // even points first: 0 and 2B
+  constexpr InnerPoints() : word() {
+    for (int i = 0; i < 64 * K; ++i) {
+      const int q = i % P;
+      const bool in = !on_face(q % E) && !on_face(q / E % E) && !on_face(q / (E * E));
+      if (i < NB * P && in) word[i / 64] |= uint64_t(1) << (i % 64);
+    }
+  }
+};
+template <int B>
+__device__ __forceinline__ bool inner_point(int lane, int k) {
+  constexpr InnerPoints<B> in;
+  return (in.word[k] >> lane) & 1;
 }
 
 template <typename T>
@@ -231,7 +268,7 @@ __device__ __forceinline__ const double* blk_hw2<double>(const DevBlocks& b) {
 template <typename T, int B, bool ACC>
 __global__ __launch_bounds__(64) void k_vmult_blocks(DevBlocks blk, const int8_t* __restrict__ clev,
                                                      const T* __restrict__ mu, const T* __restrict__ x,
-                                                     T* __restrict__ y, T* __restrict__ fslot) {
+                                                     T* __restrict__ y, T* __restrict__ fslot, bool noflux) {
   constexpr int NC = B * B * B, NB = 64 / NC;   // cells per block, blocks per wave
   constexpr int E = 2 * B + 1, P = E * E * E, W = 3 * P;
   constexpr int KP = (NB * P + 63) / 64;        // lattice points per lane
@@ -241,11 +278,8 @@ __global__ __launch_bounds__(64) void k_vmult_blocks(DevBlocks blk, const int8_t
   const int nb = int(std::min<int64_t>(NB, blk.n - blk0));   // blocks of this wave
   const int np = nb * P;
   const T* __restrict__ hw = blk_hw<T>(blk);
-  // lattice point p of the wave (block p / P) -> LDS offset of its component 0
-  auto lds_of = [&](int bl, int p) {
-    const int px = p % E, py = (p / E) % E, pz = p / (E * E);
-    return bl * W + bsplit<B>(px) + E * bsplit<B>(py) + E * E * bsplit<B>(pz);
-  };
+  // position p of block bl -> LDS offset of its component 0
+  auto lds_of = [](int bl, int p) { return bl * W + p; };
   // staging: every slot load, then every value load, issued before use;
   // points of missing blocks, Dirichlet and hanging points (and components
   // fixed by the no-normal-flux condition) store zero.  The slots stay in
@@ -255,6 +289,14 @@ __global__ __launch_bounds__(64) void k_vmult_blocks(DevBlocks blk, const int8_t
   for (int k = 0; k < KP; ++k) {
     const int pa = lane + 64 * k;
     sl[k] = pa < np ? blk.slots[blk0 * P + pa] : -1;
+  }
+  // (the cell's coefficient here, beside the staging: behind it, its two
+  // dependent loads were waited for by themselves)
+  const int bl = lane / NC, lc = lane - bl * NC;
+  T coef = T(0);
+  if (bl < nb) {
+    const int32_t c = blk.cells[(blk0 + bl) * NC + lc];
+    coef = mu[c] * T(ldexp(1.0, -int(clev[c])));
   }
   {
     T v[KP][3];
@@ -269,9 +311,15 @@ __global__ __launch_bounds__(64) void k_vmult_blocks(DevBlocks blk, const int8_t
       if (pa < NB * P) {
         const int o = lds_of(pa / P, pa % P);
         const bool f = sl[k] >= 0;
-        buf[o] = f && !slot_fixed(sl[k], 0) ? v[k][0] : T(0);
-        buf[o + P] = f && !slot_fixed(sl[k], 1) ? v[k][1] : T(0);
-        buf[o + 2 * P] = f && !slot_fixed(sl[k], 2) ? v[k][2] : T(0);
+        if (noflux) {
+          buf[o] = f && !slot_fixed(sl[k], 0) ? v[k][0] : T(0);
+          buf[o + P] = f && !slot_fixed(sl[k], 1) ? v[k][1] : T(0);
+          buf[o + 2 * P] = f && !slot_fixed(sl[k], 2) ? v[k][2] : T(0);
+        } else {
+          buf[o] = f ? v[k][0] : T(0);
+          buf[o + P] = f ? v[k][1] : T(0);
+          buf[o + 2 * P] = f ? v[k][2] : T(0);
+        }
       }
     }
   }
@@ -326,7 +374,6 @@ __global__ __launch_bounds__(64) void k_vmult_blocks(DevBlocks blk, const int8_t
     }
   }
   __syncthreads();
-  const int bl = lane / NC, lc = lane - bl * NC;
   const int ca = lc % B, cb = (lc / B) % B, cc = lc / (B * B);
   const int base = bl * W;
   T U[3][27];
@@ -343,11 +390,6 @@ __global__ __launch_bounds__(64) void k_vmult_blocks(DevBlocks blk, const int8_t
   __syncthreads();
   if constexpr (B > 1)
     for (int e = lane; e < NB * W; e += 64) buf[e] = T(0);
-  T coef = T(0);
-  if (bl < nb) {
-    const int32_t c = blk.cells[(blk0 + bl) * NC + lc];
-    coef = mu[c] * T(ldexp(1.0, -int(clev[c])));
-  }
   cellop::apply_cell(U);
   __syncthreads();
   if constexpr (B == 1) {   // a single cell's points are its own
@@ -426,22 +468,18 @@ __global__ __launch_bounds__(64) void k_vmult_blocks(DevBlocks blk, const int8_t
 #pragma unroll
   for (int k = 0; k < KP; ++k) {
     if (sl[k] < 0) continue;
-    const int pa = lane + 64 * k, p = pa % P;
-    const int o = lds_of(pa / P, p);
-    const T v0 = slot_fixed(sl[k], 0) ? T(0) : buf[o];
-    const T v1 = slot_fixed(sl[k], 1) ? T(0) : buf[o + P];
-    const T v2 = slot_fixed(sl[k], 2) ? T(0) : buf[o + 2 * P];
-    const int px = p % E, py = (p / E) % E, pz = p / (E * E);
-    const bool inner = px > 0 && px < E - 1 && py > 0 && py < E - 1 && pz > 0 && pz < E - 1;
-    T* yp = y + 3 * int64_t(slot_node(sl[k]));
-    if (inner && ACC) {
-      yp[0] += v0, yp[1] += v1, yp[2] += v2;
-    } else if (inner) {
-      yp[0] = v0, yp[1] = v1, yp[2] = v2;
-    } else {
-      T* fs = fslot + 3 * ((blk0 + pa / P) * P + p);
-      fs[0] = v0, fs[1] = v1, fs[2] = v2;
+    const int pa = lane + 64 * k;
+    const int o = lds_of(pa / P, pa % P);
+    T v0 = buf[o], v1 = buf[o + P], v2 = buf[o + 2 * P];
+    if (noflux) {
+      if (slot_fixed(sl[k], 0)) v0 = T(0);
+      if (slot_fixed(sl[k], 1)) v1 = T(0);
+      if (slot_fixed(sl[k], 2)) v2 = T(0);
     }
+    const bool inner = inner_point<B>(lane, k);
+    T* yp = inner ? y + 3 * int64_t(slot_node(sl[k])) : fslot + 3 * (blk0 * P + pa);
+    if (inner && ACC) v0 += yp[0], v1 += yp[1], v2 += yp[2];
+    yp[0] = v0, yp[1] = v1, yp[2] = v2;
   }
 }
 
@@ -1782,10 +1820,7 @@ __global__ __launch_bounds__(64) void k_grad_blocks(DevBlocks blk, DevLevel L, D
   const int64_t blk0 = int64_t(blockIdx.x) * NB;
   const int nb = int(std::min<int64_t>(NB, blk.n - blk0));
   const int np = nb * PP;
-  auto lds_of = [&](int bl, int q) {
-    const int px = q % E, py = (q / E) % E, pz = q / (E * E);
-    return bl * W + bsplit<B>(px) + E * bsplit<B>(py) + E * E * bsplit<B>(pz);
-  };
+  auto lds_of = [](int bl, int q) { return bl * W + q; };
   for (int e = lane; e < NB * W; e += 64) buf[e] = 0.0;
   const int bl = lane / NC, lc = lane - bl * NC;
   const int ca = lc % B, cb = (lc / B) % B, cc = lc / (B * B);
@@ -1847,8 +1882,7 @@ __global__ __launch_bounds__(64) void k_grad_blocks(DevBlocks blk, DevLevel L, D
     const double v0 = slot_fixed(sl[k], 0) ? 0.0 : buf[o];
     const double v1 = slot_fixed(sl[k], 1) ? 0.0 : buf[o + PP];
     const double v2 = slot_fixed(sl[k], 2) ? 0.0 : buf[o + 2 * PP];
-    const int px = q % E, py = (q / E) % E, pz = q / (E * E);
-    const bool inner = px > 0 && px < E - 1 && py > 0 && py < E - 1 && pz > 0 && pz < E - 1;
+    const bool inner = inner_point<B>(lane, k);
     double* yp = uo + 3 * int64_t(slot_node(sl[k]));
     if (inner) {
       yp[0] += v0, yp[1] += v1, yp[2] += v2;
@@ -2188,10 +2222,7 @@ __global__ __launch_bounds__(64) void k_div_blocks(DevBlocks blk, DevLevel L, De
   const int64_t blk0 = int64_t(blockIdx.x) * NB;
   const int nb = int(std::min<int64_t>(NB, blk.n - blk0));
   const int np = nb * PP;
-  auto lds_of = [&](int bl, int q) {
-    const int px = q % E, py = (q / E) % E, pz = q / (E * E);
-    return bl * W + bsplit<B>(px) + E * bsplit<B>(py) + E * E * bsplit<B>(pz);
-  };
+  auto lds_of = [](int bl, int q) { return bl * W + q; };
   {
     int32_t sl[KP];
 #pragma unroll
@@ -2521,16 +2552,16 @@ void vmult_impl(const DevLevel& L, const T* x, T* y, hipStream_t s, bool init, b
   const unsigned g2 = unsigned((L.blk2.n + 7) / 8), g1 = unsigned((L.blk1.n + 63) / 64);
   T *fs2 = fs + 3 * L.fslot_blk2, *fs1 = fs + 3 * L.fslot_blk1;
   if (init) {
-    if (L.blk4.n) k_vmult_blocks<T, 4, false><<<unsigned(L.blk4.n), 64, 0, s>>>(L.blk4, L.clev, mu_of<T>(L), x, y, fs);
-    if (L.blk2.n) k_vmult_blocks<T, 2, false><<<g2, 64, 0, s>>>(L.blk2, L.clev, mu_of<T>(L), x, y, fs2);
-    if (L.blk1.n) k_vmult_blocks<T, 1, false><<<g1, 64, 0, s>>>(L.blk1, L.clev, mu_of<T>(L), x, y, fs1);
+    if (L.blk4.n) k_vmult_blocks<T, 4, false><<<unsigned(L.blk4.n), 64, 0, s>>>(L.blk4, L.clev, mu_of<T>(L), x, y, fs, L.noflux);
+    if (L.blk2.n) k_vmult_blocks<T, 2, false><<<g2, 64, 0, s>>>(L.blk2, L.clev, mu_of<T>(L), x, y, fs2, L.noflux);
+    if (L.blk1.n) k_vmult_blocks<T, 1, false><<<g1, 64, 0, s>>>(L.blk1, L.clev, mu_of<T>(L), x, y, fs1, L.noflux);
     if (L.n_outer)
       k_face_gather<T, true><<<grid_for(L.n_outer), kBlock, 0, s>>>(L.n_outer, L.outer_node, L.outer_ptr, L.outer_ent,
                                                                    fs, y);
   } else {
-    if (L.blk4.n) k_vmult_blocks<T, 4, true><<<unsigned(L.blk4.n), 64, 0, s>>>(L.blk4, L.clev, mu_of<T>(L), x, y, fs);
-    if (L.blk2.n) k_vmult_blocks<T, 2, true><<<g2, 64, 0, s>>>(L.blk2, L.clev, mu_of<T>(L), x, y, fs2);
-    if (L.blk1.n) k_vmult_blocks<T, 1, true><<<g1, 64, 0, s>>>(L.blk1, L.clev, mu_of<T>(L), x, y, fs1);
+    if (L.blk4.n) k_vmult_blocks<T, 4, true><<<unsigned(L.blk4.n), 64, 0, s>>>(L.blk4, L.clev, mu_of<T>(L), x, y, fs, L.noflux);
+    if (L.blk2.n) k_vmult_blocks<T, 2, true><<<g2, 64, 0, s>>>(L.blk2, L.clev, mu_of<T>(L), x, y, fs2, L.noflux);
+    if (L.blk1.n) k_vmult_blocks<T, 1, true><<<g1, 64, 0, s>>>(L.blk1, L.clev, mu_of<T>(L), x, y, fs1, L.noflux);
     if (L.n_outer)
       k_face_gather<T, false><<<grid_for(L.n_outer), kBlock, 0, s>>>(L.n_outer, L.outer_node, L.outer_ptr, L.outer_ent,
                                                                     fs, y);
