@@ -76,7 +76,7 @@ struct DevLevel {
   // the prolongation from the level below (CSR of the LevelDev) and of its
   // transpose, the diagonal of the unit element matrix [192]
   bool q3 = false;
-  float* q3_halo_f = nullptr;       // operator halo slots (q3_halo_words entries)
+  float* q3_halo_f = nullptr;       // the larger levels' operator halo slots (q3_halo_words entries)
   double* q3_halo_d = nullptr;
   const double* q3_Pw = nullptr;
   const double* q3_Rw = nullptr;
@@ -358,8 +358,12 @@ void set_element_constants(const double* khat_diag81, const double* bhat8x81, co
 // operator writes every entry of y (identity rows on constrained dofs), or
 // adds the cell terms to the free entries when accumulating.
 void set_q3_constants(const double* N, const double* D, const double* w, const double* P2, const double* M2);
-template <typename T>
-void launch_vmult_q3(const DevLevel& L, const T* x, T* y, bool accumulate, hipStream_t s);
+namespace owner {
+enum class Op;   // owner_kernel.h
+}
+template <owner::Op OP, typename T>
+void launch_owner_q3(const DevLevel& L, const T* x, const T* b, const T* minv, T* d, T* y, double alpha, double beta,
+                     double it0, hipStream_t s);
 // scratch vector k (0 or 1) of level L's separable transfers, precision T
 template <typename T>
 inline T* tr_scratch(const DevLevel& L, int k);
@@ -372,7 +376,7 @@ inline double* tr_scratch<double>(const DevLevel& L, int k) {
   return k ? L.tr_s2_d : L.tr_s1_d;
 }
 
-// entries of a Q3 level's operator halo buffer (n cells per edge)
+// entries of a Q3 level's operator halo buffer (n cells per edge; 0: none)
 int64_t q3_halo_words(int64_t n);
 // separable transfers between a Q3 lattice level F and the level below
 // (three one-axis passes through F's scratch vectors); t may be null

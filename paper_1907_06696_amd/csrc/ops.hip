@@ -2506,6 +2506,10 @@ void launch_brick(const DevLevel& L, const T* x, T* y, T* halo, bool init, hipSt
 template <owner::Op OP, typename T>
 void launch_owner(const DevLevel& L, const T* x, const T* b, const T* minv, T* d, T* y, double alpha, double beta,
                   double it0, hipStream_t s) {
+  if (L.q3) {
+    launch_owner_q3<OP, T>(L, x, b, minv, d, y, alpha, beta, it0, s);
+    return;
+  }
   const int64_t n = L.uniform ? L.n_edge : L.grid_edge;
   const owner::Args<T> a{int(n), mu_of<T>(L), x, b, minv, d, y, T(alpha), T(beta), T(it0), L.grid_node, L.grid_cell};
   const unsigned g1 = unsigned(n * n * n / 8), g2 = unsigned(n * n * n / 16);
@@ -2536,13 +2540,9 @@ void vmult_impl(const DevLevel& L, const T* x, T* y, hipStream_t s, bool init, b
     }
     return;
   }
-  if (L.grid_edge) {
+  if (L.grid_edge || L.q3) {
     if (init) launch_owner<owner::Op::Apply, T>(L, x, nullptr, nullptr, nullptr, y, 0.0, 0.0, 0.0, s);
     else launch_owner<owner::Op::Add, T>(L, x, nullptr, nullptr, nullptr, y, 0.0, 0.0, 0.0, s);
-    return;
-  }
-  if (L.q3) {   // owner-computes: no initialisation kernel 
-    launch_vmult_q3<T>(L, x, y, !init, s);
     return;
   }
   // the blocks store their inner points and leave the others in slots, which
@@ -2582,9 +2582,9 @@ template <typename T>
 void launch_vmult_free(const DevLevel& L, const T* x, T* y, hipStream_t s) {
   vmult_impl<T>(L, x, y, s, true, true);
 }
-const uint8_t* step_mask(const DevLevel& L) { return !L.q3 && !L.uniform && !L.grid_edge ? L.cmask : nullptr; }
+const uint8_t* step_mask(const DevLevel& L) { return !L.uniform ? L.cmask : nullptr; }
 
-bool smoother_fuses(const DevLevel& L) { return L.grid_edge || (L.uniform && L.n_edge <= kFusedMaxEdge); }
+bool smoother_fuses(const DevLevel& L) { return L.q3 || L.grid_edge || (L.uniform && L.n_edge <= kFusedMaxEdge); }
 template <typename T>
 void launch_fused_first(const DevLevel& L, const T* b, const T* minv, T* d, T* y, double it0, double alpha,
                         double beta, hipStream_t s) {

@@ -1,35 +1,17 @@
 // Device kernels of the Q3-Q2 pair (k = 2 of Sec. 2.1) on uniform lattice
 // levels (see q3.h for the numbering).
 //
-// One wavefront per cell: lane l = x + 4 y + 16 z stands for the tensor
-// point (x, y, z) of the cell's 4 x 4 x 4 nodes and, after interpolation, of
-// its 4 x 4 x 4 Gauss points.  A one-dimensional 4 x 4 contraction along an
-// axis is four reads of other lanes and four multiply-adds per lane, so the
-// sum-factorised operator keeps one value per lane and component:
-//   interpolate u to the Gauss points (3 axes x 3 components),
-//   differentiate there with the Gauss-collocation derivative (9 sweeps),
-//   F_cd = mu h w_q (d_d u_c + d_c u_d),
-//   y_c = N^T N^T N^T sum_d D_d^T F_cd (9 + 9 transposed sweeps).
-// In the operator the x and y contractions read the other lanes through DPP
-// (quad broadcast along x, row rotation by 4, 8, 12 lanes along y: VALU
-// operand modifiers, no LDS traffic) and the z contraction, across rows,
-// through __shfl (ds_bpermute); the other kernels use __shfl throughout.
-// The operator's results are summed over a 2 x 2 x 2 block of cells (one
-// workgroup, a wavefront per cell): each wavefront stores its 3 x 64 results
-// in its own LDS slot, and each thread of the write-back sums the (up to 8)
-// slot entries of one block lattice point and component.  Owner computes, as
-// in the Q2 brick kernel: a lattice point belongs to the block whose
-// half-open box [6b, 6b + 6) holds it (the last block along an axis also owns
-// the closing plane); the block writes the points it owns (y = its sum, or
-// y = x on constrained points: identity rows; accumulating, y += its sum on
-// free points) and stores the sums of the 127 points of its high faces, owned
-// by upper neighbours, in its halo slot; a second kernel adds, for every
-// point on a block's low face, the neighbours' slot values.  No atomics and
-// no separate initialisation of y.  Constrained (boundary) nodes are read as
-// zero.
+// The operator, with the smoother's updates, is in q3_owner.h.  The other
+// kernels (right-hand side, divergence, gradient, pressure) take one wavefront
+// per cell: lane l = x + 4 y + 16 z stands for the tensor point (x, y, z) of
+// the cell's 4 x 4 x 4 nodes and, after interpolation, of its 4 x 4 x 4 Gauss
+// points, and a one-dimensional 4 x 4 contraction along an axis is four reads
+// of other lanes (__shfl) and four multiply-adds per lane.  Constrained
+// (boundary) nodes are read as zero.
 #include <hip/hip_runtime.h>
 
 #include "ops.h"
+#include "q3_owner.h"
 
 namespace mfgmg {
 
@@ -42,6 +24,10 @@ __constant__ double c_q3P[12];    // P2[q][i]: Q2 pressure basis at the Gauss po
 __constant__ double c_q3M2[9];    // 1D Q2 mass
 
 constexpr int kBlock = 256;
+// Largest level of the fused kernel.  One smoothing step, FP64: 16^3 13.3 us
+// fused, 18.6 us as brick and halo kernels; 32^3 72 us fused (each cell is
+// computed 2.8 times or more), 53 us as brick (28) and halo (25).
+constexpr int kQ3SmallEdge = 16;
 
 inline unsigned grid_for(int64_t n, int block = kBlock, int64_t cap = 1 << 20) {
   int64_t g = (n + block - 1) / block;
@@ -77,59 +63,6 @@ __device__ __forceinline__ void col_of(const double* M, int lane, T (&c)[4]) {
   for (int q = 0; q < 4; ++q) c[q] = T(M[4 * q + a]);
 }
 
-// DPP move of a 32-bit value (CTRL: quad_perm / row_ror encodings of GFX9)
-template <int CTRL>
-__device__ __forceinline__ int dpp_i(int v) {
-  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, false);
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-  return __builtin_bit_cast(float, dpp_i<CTRL>(__builtin_bit_cast(int, v)));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v) {
-  const long long b = __builtin_bit_cast(long long, v);
-  const int lo = dpp_i<CTRL>(int(b & 0xffffffffLL)), hi = dpp_i<CTRL>(int(b >> 32));
-  return __builtin_bit_cast(double, (static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
-}
-constexpr int kQuadBcast[4] = {0x00, 0x55, 0xAA, 0xFF};   // quad_perm: every lane of a quad reads lane a
-constexpr int kRowRor[4] = {0, 0x124, 0x128, 0x12C};      // row_ror by 0, 4, 8, 12 lanes
-
-// x contraction: c[a] the lane's coefficient of quad lane a (row_of / col_of)
-template <typename T>
-__device__ __forceinline__ T sweep_x(T v, const T (&c)[4]) {
-  return c[0] * dpp<kQuadBcast[0]>(v) + c[1] * dpp<kQuadBcast[1]>(v) + c[2] * dpp<kQuadBcast[2]>(v) +
-         c[3] * dpp<kQuadBcast[3]>(v);
-}
-// y contraction: r[k] the lane's coefficient of the value that the rotation by
-// 4k lanes brings (the coefficient of that value's y coordinate)
-template <typename T>
-__device__ __forceinline__ T sweep_y(T v, const T (&r)[4]) {
-  return r[0] * v + r[1] * dpp<kRowRor[1]>(v) + r[2] * dpp<kRowRor[2]>(v) + r[3] * dpp<kRowRor[3]>(v);
-}
-// y coordinate (lane bits 2-3) of the lane each rotation reads
-__device__ __forceinline__ void rot_sources(int lane, int (&src)[4]) {
-  const int yv = (lane >> 2) & 3;
-  src[0] = yv;
-  src[1] = dpp_i<kRowRor[1]>(yv);
-  src[2] = dpp_i<kRowRor[2]>(yv);
-  src[3] = dpp_i<kRowRor[3]>(yv);
-}
-// coefficients of a y contraction in rotation order: row (out(q) = sum_a M[q][a] v(a))
-// or column (out(a) = sum_q M[q][a] v(q)) of M for the lane's y coordinate
-template <typename T>
-__device__ __forceinline__ void rot_row(const double* M, int lane, const int (&src)[4], T (&r)[4]) {
-  const int q = (lane >> 2) & 3;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) r[k] = T(M[4 * q + src[k]]);
-}
-template <typename T>
-__device__ __forceinline__ void rot_col(const double* M, int lane, const int (&src)[4], T (&r)[4]) {
-  const int a = (lane >> 2) & 3;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) r[k] = T(M[4 * src[k] + a]);
-}
-
 struct Q3Cell {
   int64_t node;
   bool bnd;
@@ -141,126 +74,6 @@ struct Q3Cell {
     bnd = X == 0 || Y == 0 || Z == 0 || X == m - 1 || Y == m - 1 || Z == m - 1;
   }
 };
-
-constexpr int kQ3B = 2;                         // cells per block edge
-constexpr int kQ3E = 3 * kQ3B + 1;              // lattice points per block edge
-constexpr int kQ3P = kQ3E * kQ3E * kQ3E;        // lattice points per block
-constexpr int kQ3H = kQ3P - (kQ3E - 1) * (kQ3E - 1) * (kQ3E - 1);   // high-face points per block (127)
-
-// index of a high-face point of the block lattice in the block's halo slot
-// (p_x = 6: the 7 x 7 plane; else p_y = 6: 6 x 7; else p_z = 6: 6 x 6)
-__device__ __forceinline__ int q3_halo_index(int px, int py, int pz) {
-  constexpr int L = kQ3E - 1;
-  if (px == L) return py + kQ3E * pz;
-  if (py == L) return kQ3E * kQ3E + px + L * pz;
-  return kQ3E * kQ3E + L * kQ3E + px + L * py;
-}
-
-template <typename T, bool ACC>
-__global__ __launch_bounds__(64 * kQ3B * kQ3B * kQ3B) void k_vmult_q3(int64_t n, const T* __restrict__ mu,
-                                                                     const T* __restrict__ x, T* __restrict__ y,
-                                                                     T* __restrict__ halo) {
-  constexpr int NW = kQ3B * kQ3B * kQ3B;
-  __shared__ T slot[NW][3][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t nb = n / kQ3B;
-  const int64_t bx = blockIdx.x % nb, by = (blockIdx.x / nb) % nb, bz = blockIdx.x / (nb * nb);
-  const int cx = w % kQ3B, cy = (w / kQ3B) % kQ3B, cz = w / (kQ3B * kQ3B);
-  const int64_t c = (bx * kQ3B + cx) + n * ((by * kQ3B + cy) + n * (bz * kQ3B + cz));
-  const Q3Cell qc(n, c, lane);
-  T u[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) u[k] = qc.bnd ? T(0) : x[3 * qc.node + k];
-  int src[4];
-  rot_sources(lane, src);
-  T Nx[4], Ny[4], Nz[4];
-  row_of<0>(c_q3N, lane, Nx), rot_row(c_q3N, lane, src, Ny), row_of<2>(c_q3N, lane, Nz);
-#pragma unroll
-  for (int k = 0; k < 3; ++k) u[k] = sweep<2>(sweep_y(sweep_x(u[k], Nx), Ny), lane, Nz);
-  T Dx[4], Dy[4], Dz[4];
-  row_of<0>(c_q3D, lane, Dx), rot_row(c_q3D, lane, src, Dy), row_of<2>(c_q3D, lane, Dz);
-  T g[3][3];   // g[c][d] = d_d u_c at the lane's Gauss point
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    g[k][0] = sweep_x(u[k], Dx);
-    g[k][1] = sweep_y(u[k], Dy);
-    g[k][2] = sweep<2>(u[k], lane, Dz);
-  }
-  const T wq = T(c_q3W[lane & 3] * c_q3W[(lane >> 2) & 3] * c_q3W[lane >> 4]);
-  const T coef = mu[c] / T(n) * wq;
-  T F[3][3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int b = 0; b < 3; ++b) F[a][b] = coef * (g[a][b] + g[b][a]);
-  col_of<0>(c_q3D, lane, Dx), rot_col(c_q3D, lane, src, Dy), col_of<2>(c_q3D, lane, Dz);
-  col_of<0>(c_q3N, lane, Nx), rot_col(c_q3N, lane, src, Ny), col_of<2>(c_q3N, lane, Nz);
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    // every lane takes part in the cross-lane reads; boundary lanes drop the result after
-    const T t = sweep_x(F[k][0], Dx) + sweep_y(F[k][1], Dy) + sweep<2>(F[k][2], lane, Dz);
-    const T o = sweep<2>(sweep_y(sweep_x(t, Nx), Ny), lane, Nz);
-    slot[w][k][lane] = qc.bnd ? T(0) : o;
-  }
-  __syncthreads();
-  // write-back: point p of the block lattice gathers, per axis, the cells
-  // (0 or 1) whose local coordinate p - 3 cell lies in 0..3
-  const int64_t m = 3 * n + 1;
-  for (int e = threadIdx.x; e < 3 * kQ3P; e += blockDim.x) {
-    const int p = e / 3, k = e - 3 * p;
-    const int px = p % kQ3E, py = (p / kQ3E) % kQ3E, pz = p / (kQ3E * kQ3E);
-    const int64_t X = 3 * kQ3B * bx + px, Y = 3 * kQ3B * by + py, Z = 3 * kQ3B * bz + pz;
-    const bool own = (px < kQ3E - 1 || bx == nb - 1) && (py < kQ3E - 1 || by == nb - 1) &&
-                     (pz < kQ3E - 1 || bz == nb - 1);
-    const int64_t d = 3 * (X + m * (Y + m * Z)) + k;
-    if (X == 0 || Y == 0 || Z == 0 || X == m - 1 || Y == m - 1 || Z == m - 1) {
-      if (!ACC && own) y[d] = x[d];   // identity row (every constrained point has one owner)
-      continue;
-    }
-    T v = T(0);
-    for (int ccz = 0; ccz < kQ3B; ++ccz) {
-      const int lz = pz - 3 * ccz;
-      if (lz < 0 || lz > 3) continue;
-      for (int ccy = 0; ccy < kQ3B; ++ccy) {
-        const int ly = py - 3 * ccy;
-        if (ly < 0 || ly > 3) continue;
-        for (int ccx = 0; ccx < kQ3B; ++ccx) {
-          const int lx = px - 3 * ccx;
-          if (lx < 0 || lx > 3) continue;
-          v += slot[ccx + kQ3B * (ccy + kQ3B * ccz)][k][lx + 4 * ly + 16 * lz];
-        }
-      }
-    }
-    if (own) y[d] = ACC ? y[d] + v : v;
-    else halo[(int64_t(blockIdx.x) * kQ3H + q3_halo_index(px, py, pz)) * 3 + k] = v;
-  }
-}
-
-// Adds the halo values of its lower neighbour blocks into every free lattice
-// point that lies on a block's low face (one thread per point, 3 components).
-template <typename T>
-__global__ __launch_bounds__(256) void k_q3_halo_add(int64_t n, const T* __restrict__ halo, T* __restrict__ y) {
-  const int64_t nb = n / kQ3B, m = 3 * n + 1, L = 3 * kQ3B;
-  // points with a coordinate on an inner block plane (a multiple of 6 in 6 .. m - 7)
-  const int64_t node = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  if (node >= m * m * m) return;
-  const int64_t X = node % m, Y = (node / m) % m, Z = node / (m * m);
-  if (X == 0 || Y == 0 || Z == 0 || X == m - 1 || Y == m - 1 || Z == m - 1) return;
-  const bool fx = X % L == 0, fy = Y % L == 0, fz = Z % L == 0;
-  if (!fx && !fy && !fz) return;
-  const int64_t ox = X / L < nb ? X / L : nb - 1, oy = Y / L < nb ? Y / L : nb - 1, oz = Z / L < nb ? Z / L : nb - 1;
-  const int px = int(X - L * ox), py = int(Y - L * oy), pz = int(Z - L * oz);
-  T a0 = T(0), a1 = T(0), a2 = T(0);
-  for (int sv = 1; sv < 8; ++sv) {
-    const int sx = sv & 1, sy = (sv >> 1) & 1, sz = sv >> 2;
-    if ((sx && !fx) || (sy && !fy) || (sz && !fz)) continue;
-    const int64_t nbk = (ox - sx) + nb * ((oy - sy) + nb * (oz - sz));
-    const T* h = halo + (nbk * kQ3H + q3_halo_index(px + int(L) * sx, py + int(L) * sy, pz + int(L) * sz)) * 3;
-    a0 += h[0], a1 += h[1], a2 += h[2];
-  }
-  T* yp = y + 3 * node;
-  yp[0] += a0, yp[1] += a1, yp[2] += a2;
-}
 
 // ---------------------------------------------------------- transfers
 // Between two Q3 lattice levels the prolongation is the tensor product of one
@@ -572,24 +385,34 @@ double* q3_halo<double>(const DevLevel& L) {
   return L.q3_halo_d;
 }
 
-int64_t q3_halo_words(int64_t n) {
-  const int64_t nb = n / kQ3B;
-  return nb * nb * nb * kQ3H * 3;
-}
+int64_t q3_halo_words(int64_t n) { return n <= kQ3SmallEdge ? 0 : n * n * n / 16 * q3own::Large::halo * 3; }
 
-template <typename T>
-void launch_vmult_q3(const DevLevel& L, const T* x, T* y, bool accumulate, hipStream_t s) {
-  // uniform levels have n = 2^l >= 2 cells per edge: whole 2 x 2 x 2 blocks
-  const int64_t n = L.n_edge, nb = n / kQ3B, m = 3 * n + 1;
+// levels have n = 2^l >= 2 cells per edge
+template <owner::Op OP, typename T>
+void launch_owner_q3(const DevLevel& L, const T* x, const T* b, const T* minv, T* d, T* y, double alpha, double beta,
+                     double it0, hipStream_t s) {
+  const int64_t n = L.n_edge;
+  const q3own::Args<T> a{int(n), mu_of<T>(L), x, b, minv, d, y, T(alpha), T(beta), T(it0)};
+  if (n <= kQ3SmallEdge) {
+    q3own::k_owner_q3<T, OP><<<unsigned(n * n * n / 8), q3own::Brick::threads, 0, s>>>(a);
+    return;
+  }
+  constexpr owner::Op sums = OP == owner::Op::Add || OP == owner::Op::First ? OP : owner::Op::Apply;
+  const int64_t m = 3 * n + 1, waves = m * m * ((3 * m + 63) / 64);
   T* halo = q3_halo<T>(L);
-  if (accumulate)
-    k_vmult_q3<T, true><<<unsigned(nb * nb * nb), 64 * kQ3B * kQ3B * kQ3B, 0, s>>>(n, mu_of<T>(L), x, y, halo);
-  else
-    k_vmult_q3<T, false><<<unsigned(nb * nb * nb), 64 * kQ3B * kQ3B * kQ3B, 0, s>>>(n, mu_of<T>(L), x, y, halo);
-  if (nb > 1) k_q3_halo_add<T><<<grid_for(m * m * m, 256, int64_t(1) << 30), 256, 0, s>>>(n, halo, y);
+  q3own::k_brick_q3<T, sums><<<unsigned(n * n * n / 16), q3own::Large::threads, 0, s>>>(a, halo);
+  q3own::k_halo_q3<T, OP><<<unsigned((waves + 3) / 4), 256, 0, s>>>(a, halo);
 }
-template void launch_vmult_q3<float>(const DevLevel&, const float*, float*, bool, hipStream_t);
-template void launch_vmult_q3<double>(const DevLevel&, const double*, double*, bool, hipStream_t);
+#define MFGMG_Q3_OP(T, OP)                                                                                       \
+  template void launch_owner_q3<owner::Op::OP, T>(const DevLevel&, const T*, const T*, const T*, T*, T*, double, \
+                                                  double, double, hipStream_t);
+#define MFGMG_Q3_OPS(T)                                                                        \
+  MFGMG_Q3_OP(T, Apply) MFGMG_Q3_OP(T, Add) MFGMG_Q3_OP(T, Residual) MFGMG_Q3_OP(T, First) \
+  MFGMG_Q3_OP(T, Start) MFGMG_Q3_OP(T, Step) MFGMG_Q3_OP(T, Last)
+MFGMG_Q3_OPS(float)
+MFGMG_Q3_OPS(double)
+#undef MFGMG_Q3_OPS
+#undef MFGMG_Q3_OP
 
 // fine level F (m_f = 3n + 1), coarse m_c = 3 n / 2 + 1: x, then y, then z
 template <typename T>
