@@ -1084,6 +1084,157 @@ __global__ __launch_bounds__(kBlock) void k_restrict_z(int nc, const T* __restri
   }
 }
 
+// Transfers of small levels (coarse levels up to kTileMaxCoarse cells per edge)
+// in one kernel each, the three axes one after the other in LDS: a launch costs
+// more than a tile's overlapping reads there, and a launch's chain of loads and
+// barriers bounds them.  Restriction (4 x 4 x 4 coarse nodes of 11 x 11 x 11
+// fine ones a workgroup): from 32^3 FP32 14.5 us as three kernels, 7.5 us; from
+// 16^3 FP64 11.1 us, 6.8 us.  MAP: levels under u . n = 0 whose cells are all of
+// one size, stored in the general order, component c fixed on the two faces
+// normal to axis c only; as gathers over the transfer matrix (Morton order) the
+// restriction from 32^3 took 18.2 us FP64 (13.7), the prolongation (8 x 8 x 8
+// fine nodes a workgroup) 27.9 us (12.6).  Without a map the prolongation stays
+// with k_prolong_rows (4.1 to 6.8 us up to 32^3).
+constexpr int kTileMaxCoarse = 16;
+template <bool MAP>
+__device__ __forceinline__ bool tile_free(int m, int X, int Y, int Z, int q) {
+  if (X < 0 || Y < 0 || Z < 0 || X >= m || Y >= m || Z >= m) return false;
+  if constexpr (MAP) {
+    const int w = q == 0 ? X : q == 1 ? Y : Z;
+    return w > 0 && w < m - 1;
+  }
+  return X > 0 && X < m - 1 && Y > 0 && Y < m - 1 && Z > 0 && Z < m - 1;
+}
+// entry of component q at a lattice point (node: storage node of the lattice's)
+template <bool MAP>
+__device__ __forceinline__ int tile_entry(const int32_t* node, int m, int X, int Y, int Z, int q) {
+  const int p = X + m * (Y + m * Z);
+  return 3 * (MAP ? node[p] : p) + q;
+}
+
+template <typename T, bool MAP>
+__global__ __launch_bounds__(256) void k_restrict_tile(int nc, const T* __restrict__ b, const T* __restrict__ t,
+                                                       T* __restrict__ xc, const int32_t* __restrict__ nodef,
+                                                       const int32_t* __restrict__ nodec) {
+  constexpr int C = 4, F = 2 * C + 3, RF = 3 * F, RC = 3 * C, R = 256 / RF, K = (F * F + R - 1) / R;
+  __shared__ T fine[F * F * RF], sx[F * F * RC];
+  T* sy = fine;   // [F][C][RC], once fine has been read
+  const int mc = 2 * nc + 1, mf = 4 * nc + 1, nt = (mc + C - 1) / C;
+  const int bx = int(blockIdx.x) % nt, by = int(blockIdx.x) / nt % nt, bz = int(blockIdx.x) / (nt * nt);
+  const int cx0 = C * bx, cy0 = C * by, cz0 = C * bz, fx0 = 2 * cx0 - 3, fy0 = 2 * cy0 - 3, fz0 = 2 * cz0 - 3;
+  const int w = int(threadIdx.x) % RF, r0 = int(threadIdx.x) / RF, q = w % 3;
+  T v[K];
+  int at[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int r = r0 + R * k, X = fx0 + w / 3, Y = fy0 + r % F, Z = fz0 + r / F;
+    const bool in = r0 < R && r < F * F && tile_free<MAP>(mf, X, Y, Z, q);
+    at[k] = in ? X + mf * (Y + mf * Z) : -1;
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int p = MAP ? nodef[max(at[k], 0)] : at[k];   // (loaded without a branch)
+    at[k] = at[k] < 0 ? -1 : 3 * p + q;
+  }
+  if (t) {
+    T u[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = b[max(at[k], 0)], u[k] = t[max(at[k], 0)];
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] -= u[k];
+  } else {
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = b[max(at[k], 0)];
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    if (r0 < R && r0 + R * k < F * F) fine[w + RF * (r0 + R * k)] = at[k] < 0 ? T(0) : v[k];
+  __syncthreads();
+  // coarse point c (tile and lattice coordinates of the same parity) from the
+  // fine points 2c .. 2c + 6 of the tile, D words apart
+  auto gather = [](const T* s, int D, int c) {
+    const T* p = s + 2 * c * D;
+    const bool odd = c & 1;
+    const T near = p[2 * D] + p[4 * D], far = p[odd ? 2 * D : 0] + p[odd ? 4 * D : 6 * D];
+    return p[3 * D] + (odd ? T(0.75) : T(0.375)) * near + (odd ? T(0) : T(-0.125) * far);
+  };
+  // (fixed trip counts, so that a pass's LDS reads are in flight together)
+#pragma unroll
+  for (int k = 0; k < (F * F * RC + 255) / 256; ++k) {
+    const int e = threadIdx.x + 256 * k;
+    if (e < F * F * RC) sx[e] = gather(fine + RF * (e / RC) + e % 3, 3, e % RC / 3);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < (F * C * RC + 255) / 256; ++k) {
+    const int e = threadIdx.x + 256 * k;
+    if (e < F * C * RC) sy[e] = gather(sx + RC * F * (e / (C * RC)) + e % RC, RC, e / RC % C);
+  }
+  __syncthreads();
+  static_assert(C * C * RC <= 256);
+  const int e = threadIdx.x, X = cx0 + e % RC / 3, Y = cy0 + e / RC % C, cz = e / (C * RC), Z = cz0 + cz;
+  if (e >= C * C * RC || X >= mc || Y >= mc || Z >= mc) return;
+  const T s = gather(sy + e % (C * RC), C * RC, cz);
+  xc[tile_entry<MAP>(nodec, mc, X, Y, Z, e % 3)] = tile_free<MAP>(mc, X, Y, Z, e % 3) ? s : T(0);
+}
+
+template <typename T, bool MAP>
+__global__ __launch_bounds__(256) void k_prolong_tile(int nc, const T* __restrict__ xc, T* __restrict__ xf, bool add,
+                                                      const int32_t* __restrict__ nodef,
+                                                      const int32_t* __restrict__ nodec) {
+  constexpr int F = 8, C = F / 2 + 1, RC = 3 * C, RF = 3 * F, K = F * F * RF / 256;
+  __shared__ T sc[C * C * RC], sx[C * C * RF], sy[C * F * RF];
+  const int mc = 2 * nc + 1, mf = 4 * nc + 1, nt = (mf + F - 1) / F;
+  const int bx = int(blockIdx.x) % nt, by = int(blockIdx.x) / nt % nt, bz = int(blockIdx.x) / (nt * nt);
+  int at[K];
+  T old[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int e = threadIdx.x + 256 * k, q = e % 3;
+    const int X = F * bx + e % RF / 3, Y = F * by + e / RF % F, Z = F * bz + e / (RF * F);
+    const bool in = X < mf && Y < mf && Z < mf;
+    at[k] = in ? tile_entry<MAP>(nodef, mf, X, Y, Z, q) : -1;
+    old[k] = add && in ? xf[at[k]] : T(0);
+    // a fixed component receives nothing: its row is marked by the complement
+    if (in && !tile_free<MAP>(mf, X, Y, Z, q)) at[k] = -2 - at[k];
+  }
+#pragma unroll
+  for (int k = 0; k < (C * C * RC + 255) / 256; ++k) {
+    const int e = threadIdx.x + 256 * k, q = e % 3;
+    const int X = F / 2 * bx + e % RC / 3, Y = F / 2 * by + e / RC % C, Z = F / 2 * bz + e / (RC * C);
+    const bool in = e < C * C * RC && tile_free<MAP>(mc, X, Y, Z, q);
+    const T v = xc[in ? tile_entry<MAP>(nodec, mc, X, Y, Z, q) : 0];
+    if (e < C * C * RC) sc[e] = in ? v : T(0);
+  }
+  __syncthreads();
+  // fine point l of the tile from its coarse points, D words apart
+  auto combine = [](const T* s, int D, int l) {
+    const T* p = s + 2 * (l >> 2) * D;
+    const int r = l & 3;
+    const T p0 = p[0], p1 = p[D], p2 = p[2 * D];
+    const T odd = (r == 1 ? T(0.375) : T(-0.125)) * p0 + T(0.75) * p1 + (r == 1 ? T(-0.125) : T(0.375)) * p2;
+    return r & 1 ? odd : r ? p1 : p0;
+  };
+#pragma unroll
+  for (int k = 0; k < (C * C * RF + 255) / 256; ++k) {
+    const int e = threadIdx.x + 256 * k;
+    if (e < C * C * RF) sx[e] = combine(sc + RC * (e / RF) + e % 3, 3, e % RF / 3);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < (C * F * RF + 255) / 256; ++k) {
+    const int e = threadIdx.x + 256 * k;
+    if (e < C * F * RF) sy[e] = combine(sx + RF * C * (e / (F * RF)) + e % RF, RF, e / RF % F);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int e = threadIdx.x + 256 * k;
+    if (at[k] >= 0) xf[at[k]] = old[k] + combine(sy + e % (F * RF), F * RF, e / (F * RF));
+    else if (at[k] < -1 && !add) xf[-2 - at[k]] = T(0);
+  }
+}
+
 // ------------------------------------------------------------- coarse
 // The level-1 mesh (2^3 cells) has 81 free dofs under u = 0, 225 under u . n =
 // 0 and 375 with the Q3 element.
@@ -3138,6 +3289,11 @@ bool tr_has_scratch<double>(const DevLevel& F) {
   return F.tr_s1_d && F.tr_s2_d;
 }
 
+// both levels stored in the general order with cells of one size
+bool tile_pair(const DevLevel& F, const DevLevel& Cc) {
+  return F.grid_edge && Cc.grid_edge && F.grid_edge == 2 * Cc.grid_edge && Cc.grid_edge <= kTileMaxCoarse;
+}
+
 template <typename T>
 void launch_prolong_level(const DevLevel& F, const DevLevel& Cc, const int64_t* ptr, const int32_t* col,
                           const float* w, const T* xc, T* xf, bool add, hipStream_t s) {
@@ -3147,6 +3303,12 @@ void launch_prolong_level(const DevLevel& F, const DevLevel& Cc, const int64_t* 
       k_prolong_rows<T><<<unsigned((mf * mf + 3) / 4), 256, 0, s>>>(int(Cc.n_edge), xc, xf, add);
     else
       k_prolong_uniform<T><<<grid_for(F.nnode), kBlock, 0, s>>>(int(Cc.n_edge), xc, xf, add);
+    return;
+  }
+  if (tile_pair(F, Cc)) {
+    const int nt = int(4 * Cc.grid_edge + 8) / 8;
+    k_prolong_tile<T, true><<<unsigned(nt * nt * nt), 256, 0, s>>>(int(Cc.grid_edge), xc, xf, add, F.grid_node,
+                                                                   Cc.grid_node);
     return;
   }
   if (F.q3 && F.q3_pc0 && tr_has_scratch<T>(F)) {
@@ -3181,10 +3343,20 @@ void launch_restrict_level(const DevLevel& F, const DevLevel& Cc, const int64_t*
   }
   if (F.uniform && Cc.uniform && F.n_edge == 2 * Cc.n_edge && mc * mf * mf < (int64_t(1) << 31)) {
     const int nc = int(Cc.n_edge);
+    if (nc <= kTileMaxCoarse) {
+      const unsigned nt = unsigned(mc + 3) / 4;
+      k_restrict_tile<T, false><<<nt * nt * nt, 256, 0, s>>>(nc, b, t, xc, nullptr, nullptr);
+      return;
+    }
     if (nc <= kRowMaxCoarse) k_restrict_x_rows<T><<<unsigned((mf * mf + 3) / 4), 256, 0, s>>>(nc, b, t, s1);
     else k_restrict_x<T><<<grid_for(mc * mf * mf), kBlock, 0, s>>>(nc, b, t, s1);
     k_restrict_y<T><<<grid_for(mc * mc * mf), kBlock, 0, s>>>(nc, s1, s2);
     k_restrict_z<T><<<grid_for(mc * mc * mc), kBlock, 0, s>>>(nc, s2, xc);
+    return;
+  }
+  if (tile_pair(F, Cc)) {
+    const unsigned nt = unsigned(2 * Cc.grid_edge + 4) / 4;
+    k_restrict_tile<T, true><<<nt * nt * nt, 256, 0, s>>>(int(Cc.grid_edge), b, t, xc, F.grid_node, Cc.grid_node);
     return;
   }
   const uint8_t* cmf = F.noflux ? F.cmask : nullptr;
