@@ -867,17 +867,9 @@ void smooth_on(mfgmg_ctx* ctx, LevelDev& d, const T* b, T* x, bool x_zero, hipSt
     launch_fused_step<T>(d.v, t, b, minv, dd, x, alpha[3], beta[3], true, s);
     return;
   }
-  const uint8_t* mask = step_mask(d.v);
-  if (x_zero) {
-    launch_chebx_init0<T>(n, b, minv, dd, x, beta[0], s);
-  } else {
-    launch_vmult_free<T>(d.v, x, t, s);
-    launch_chebx_step<T>(n, b, t, minv, dd, x, alpha[0], beta[0], s, mask);
-  }
-  for (int k = 1; k < 4; ++k) {
-    launch_vmult_free<T>(d.v, x, t, s);
-    launch_chebx_step<T>(n, b, t, minv, dd, x, alpha[k], beta[k], s, mask);
-  }
+  if (x_zero) launch_chebx_init0<T>(n, b, minv, dd, x, beta[0], s);
+  else launch_step<T>(d.v, b, minv, dd, t, x, alpha[0], beta[0], false, s);
+  for (int k = 1; k < 4; ++k) launch_step<T>(d.v, b, minv, dd, t, x, alpha[k], beta[k], k == 3, s);
 }
 
 template <typename T>

@@ -180,19 +180,15 @@ template <typename T>
 void launch_cheb_step(int64_t n, const T* t, const T* minv, T* r, T* d, T* x, double alpha, double beta,
                       hipStream_t s);
 // the smoother's form (residual b - A x formed each step, r not stored):
-// init0 from x = 0; step: d = alpha d + beta minv (b - t), x += d (alpha = 0:
-// d is not read).  cmask (step_mask of the level): t is not read on constrained
-// dofs, whose rows are identities.
+// init0 from x = 0; step: t = A x, d = alpha d + beta minv (b - t), x += d
+// (alpha = 0: d is not read; last: d is not stored).
 template <typename T>
 void launch_chebx_init0(int64_t n, const T* b, const T* minv, T* d, T* x, double inv_theta, hipStream_t s);
 template <typename T>
-void launch_chebx_step(int64_t n, const T* b, const T* t, const T* minv, T* d, T* x, double alpha, double beta,
-                       hipStream_t s, const uint8_t* cmask);
-// constrained-component masks of the levels whose operator writes its identity
-// rows in a pass of its own (general levels), else null
-const uint8_t* step_mask(const DevLevel& L);
-// y = A x like launch_vmult (init), leaving y undefined on constrained dofs
-// where the level has a step_mask
+void launch_step(const DevLevel& L, const T* b, const T* minv, T* d, T* t, T* x, double alpha, double beta, bool last,
+                 hipStream_t s);
+// y = A x like launch_vmult (init), leaving y undefined on constrained dofs of
+// general levels
 template <typename T>
 void launch_vmult_free(const DevLevel& L, const T* x, T* y, hipStream_t s);
 

@@ -671,7 +671,10 @@ __global__ void k_chebx_init0(int64_t n, const T* __restrict__ b, const T* __res
     x[i] = di;
   }
 }
-template <typename T>
+// cmask: t is not read on constrained dofs, whose rows are identities.  LAST: d
+// is not stored, one of seven streams of a memory-bound kernel (64^3 FP64 49 ->
+// 43 us).
+template <typename T, bool LAST>
 __global__ void k_chebx_step(int64_t n, const T* __restrict__ b, const T* __restrict__ t, const T* __restrict__ minv,
                              T* __restrict__ d, T* __restrict__ x, T alpha, T beta, const uint8_t* __restrict__ cmask) {
   // alpha = 0: the first step from a given x (d is not read)
@@ -686,7 +689,7 @@ __global__ void k_chebx_step(int64_t n, const T* __restrict__ b, const T* __rest
     const T ri = b[i] - ti;
     const T di = (alpha != T(0) ? alpha * d[i] : T(0)) + beta * minv[i] * ri;
     const T xi = x0 + di;
-    d[i] = di;
+    if constexpr (!LAST) d[i] = di;
     x[i] = xi;
   }
 }
@@ -2733,7 +2736,16 @@ template <typename T>
 void launch_vmult_free(const DevLevel& L, const T* x, T* y, hipStream_t s) {
   vmult_impl<T>(L, x, y, s, true, true);
 }
-const uint8_t* step_mask(const DevLevel& L) { return !L.uniform ? L.cmask : nullptr; }
+template <typename T>
+void launch_step(const DevLevel& L, const T* b, const T* minv, T* d, T* t, T* x, double alpha, double beta, bool last,
+                 hipStream_t s) {
+  launch_vmult_free<T>(L, x, t, s);
+  const int64_t n = 3 * L.nnode;
+  const uint8_t* mask = L.uniform ? nullptr : L.cmask;   // general levels: identity rows not written
+  if (last) k_chebx_step<T, true><<<grid_for(n), kBlock, 0, s>>>(n, b, t, minv, d, x, T(alpha), T(beta), mask);
+  else k_chebx_step<T, false><<<grid_for(n), kBlock, 0, s>>>(n, b, t, minv, d, x, T(alpha), T(beta), mask);
+}
+
 
 bool smoother_fuses(const DevLevel& L) { return L.q3 || L.grid_edge || (L.uniform && L.n_edge <= kFusedMaxEdge); }
 template <typename T>
@@ -2761,6 +2773,10 @@ void launch_fused_residual(const DevLevel& L, const T* x, const T* b, T* y, hipS
 MFGMG_FUSED(float)
 MFGMG_FUSED(double)
 #undef MFGMG_FUSED
+template void launch_step<float>(const DevLevel&, const float*, const float*, float*, float*, float*, double, double,
+                                 bool, hipStream_t);
+template void launch_step<double>(const DevLevel&, const double*, const double*, double*, double*, double*, double,
+                                  double, bool, hipStream_t);
 template void launch_vmult_free<float>(const DevLevel&, const float*, float*, hipStream_t);
 template void launch_vmult_free<double>(const DevLevel&, const double*, double*, hipStream_t);
 template void launch_vmult<float>(const DevLevel&, const float*, float*, hipStream_t, bool);
@@ -2807,17 +2823,8 @@ template <typename T>
 void launch_chebx_init0(int64_t n, const T* b, const T* minv, T* d, T* x, double it, hipStream_t s) {
   k_chebx_init0<T><<<grid_for(n), kBlock, 0, s>>>(n, b, minv, d, x, T(it));
 }
-template <typename T>
-void launch_chebx_step(int64_t n, const T* b, const T* t, const T* minv, T* d, T* x, double alpha, double beta,
-                       hipStream_t s, const uint8_t* cmask) {
-  k_chebx_step<T><<<grid_for(n), kBlock, 0, s>>>(n, b, t, minv, d, x, T(alpha), T(beta), cmask);
-}
 template void launch_chebx_init0<float>(int64_t, const float*, const float*, float*, float*, double, hipStream_t);
 template void launch_chebx_init0<double>(int64_t, const double*, const double*, double*, double*, double, hipStream_t);
-template void launch_chebx_step<float>(int64_t, const float*, const float*, const float*, float*, float*, double,
-                                       double, hipStream_t, const uint8_t*);
-template void launch_chebx_step<double>(int64_t, const double*, const double*, const double*, double*, double*,
-                                        double, double, hipStream_t, const uint8_t*);
 #define MFGMG_INST_CHEB(T)                                                                                   \
   template void launch_cheb_init0<T>(int64_t, const T*, const T*, T*, T*, T*, double, hipStream_t);          \
   template void launch_cheb_init<T>(int64_t, const T*, const T*, const T*, T*, T*, T*, double, hipStream_t); \
