@@ -35,16 +35,15 @@ PEAK_FP64_TFLOPS = 78.6         # MI355X FP64 vector, published
 PEAK_FP32_TFLOPS = 157.3        # MI355X FP32 vector (packed FMA), published
 PEAK_FP32_UNPACKED_TFLOPS = 78.6   # the rate without packed FP32 instructions, which this build does not use
 PEAK_HBM_GBS = 8000.0
-# Algorithmic work of the cell kernel per cell (sum factorisation as built,
-# counting an FMA as 2 flops): 810 (interpolation) + 972 (gradients) + 297
-# (stress) + 1215 (transposed gradients) + 729 (transposed interpolation)
-FLOP_PER_CELL = 4023
-# The Q3-Q2 operator (k = 2) per cell: 36 one-dimensional contractions of 64
-# values with 4 terms each (9 interpolation, 9 derivative, 9 transposed
-# derivative, 9 transposed interpolation sweeps; 4 multiplies + 3 adds),
-# 768 for the symmetric stress (6 sums, 6 scalings per point) and 384 for
-# summing the three transposed derivatives of each component
-Q3_FLOP_PER_CELL = 36 * 64 * 7 + 768 + 384
+# Algorithmic work of the cell operator per cell in Legendre modes (an FMA
+# counts 2 flops): 486 (transform, 3 x 27 values, 6 a line of 3 on 3 axes) + 486
+# (its transpose) + 222 (the matrix's entries in mode form) + 162 (scaling by
+# mu h and summing into the nodes)
+FLOP_PER_CELL = 1356
+# The Q3-Q2 operator (k = 2) per cell in Legendre modes: 144 lines of 4 at 11
+# flops to modes and 10 back, and some 276 a lane for the matrix in mode form (12
+# lanes: plane and component)
+Q3_FLOP_PER_CELL = 144 * 11 + 144 * 10 + 12 * 276
 
 
 def parse():
@@ -156,8 +155,8 @@ SOLVER_VARIANTS = {
 def q3_section(level, centres, dr, timed, solves=True):
     """The Q3-Q2 pair (k = 2 of Sec. 2.1) on the same sinker field (8
     sinkers, DR 1e4): operator throughput, FP64 and FP32, on rotating vector
-    pairs larger than the last-level cache (one mfgmg_vmult: the output
-    initialisation and the wavefront-per-cell kernel), V-cycles, and the
+    pairs larger than the last-level cache (one mfgmg_vmult: the brick
+    and the halo kernel), V-cycles, and the
     Stokes solves to 1e-8 with the FP64 and the FP32 V-cycle (FGMRES(50))."""
     import torch
     from paper_1907_06696_amd import inputs, mfgmg
@@ -198,7 +197,7 @@ def q3_section(level, centres, dr, timed, solves=True):
                      "hbm_frac_algorithmic": round((2 * word * n + word * ncell) / t / 1e9 / PEAK_HBM_GBS, 4)}
         first[prec] = xs[0]
         del ys
-    ops["kernel"] = "k_vmult_q3 + k_q3_halo_add (one mfgmg_vmult)"
+    ops["kernel"] = "k_brick_q3 + k_halo_q3 above 16^3, else k_owner_q3 (one mfgmg_vmult)"
     out["operator"] = ops
     vc = {}
     for name, key in (("fp32", "f32"), ("fp64", "f64")):
@@ -597,13 +596,14 @@ def main():
         tr = measured_traffic(level, prec)
         # brick shape of the level (8 x 8 x 4 cells from 64 per edge up, 8 x 4 x 4 below)
         tname = f"{'double' if prec == 'f64' else 'float'}, 8, {8 if (1 << level) >= 64 else 4}, 4"
-        out = {"bound": "alu", "achieved": round(ach, 3), "peak": peak, "unit": "TFLOP/s",
-               "frac": round(ach / peak, 4), "traffic": tr["bytes"] if tr else None,
+        # 3.4 (FP64) and 6.8 (FP32) flop/B, below the vector ridge of 9.8: bound by HBM
+        out = {"bound": "hbm", "achieved": round(alg_bytes / call / 1e9, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
+               "frac": round(alg_bytes / call / 1e9 / PEAK_HBM_GBS, 4), "traffic": tr["bytes"] if tr else None,
+               "tflops": round(ach, 3), "alu_frac": round(ach / peak, 4),
                "kernel": f"k_vmult_brick<{tname}> + k_brick_halo_add<{tname}> (one mfgmg_vmult)",
                "call_us": round(call * 1e6, 2), "cell_loop_us": round(cell_loop[prec] * 1e6, 2),
-               "cell_loop_frac": round(flops / cell_loop[prec] / 1e12 / peak, 4),
+               "cell_loop_frac": round(alg_bytes / cell_loop[prec] / 1e9 / PEAK_HBM_GBS, 4),
                "flop_per_launch": flops, "alg_bytes_per_launch": alg_bytes,
-               "hbm_frac_algorithmic": round(alg_bytes / call / 1e9 / PEAK_HBM_GBS, 4),
                "hbm_frac_measured": round(tr["bytes"] / call / 1e9 / PEAK_HBM_GBS, 4) if tr else None,
                "traffic_source": tr["source"] if tr else "none for this kernel source"}
         out.update(extra or {})
