@@ -195,8 +195,8 @@ int mfgmg_smoother_lambda(const mfgmg_ctx* ctx, int32_t level, double* lambda_ou
 int mfgmg_inverse_diagonal(mfgmg_ctx* ctx, int32_t level, mfgmg_prec prec, void* dst_dev, void* stream);
 
 /* dst = A_level src: the matrix-free Q2 strain-rate operator of Sec. 2.1
- * (A_ij = int 2 mu eps(phi_i):eps(phi_j)) by sum factorisation at the 3x3x3
- * Gauss points of each cell, hanging nodes resolved in the gather and
+ * (A_ij = int 2 mu eps(phi_i):eps(phi_j), exactly integrated) factorised in
+ * each cell's Legendre modes, hanging nodes resolved in the gather and
  * condensed in the scatter, identity on constrained dofs.  src_dev, dst_dev:
  * [n_u[level]] of type float (FP32) or double (FP64); must not alias.  Async. */
 int mfgmg_vmult(mfgmg_ctx* ctx, int32_t level, mfgmg_prec prec, const void* src_dev, void* dst_dev,
