@@ -19,7 +19,7 @@ constexpr int kRedBlocks = 1024;   // partial sums of the reductions
 #define MFGMG_RESTRICT_LANES 16
 #endif
 #ifndef MFGMG_PROLONG_LANES
-#define MFGMG_PROLONG_LANES 4
+#define MFGMG_PROLONG_LANES 2
 #endif
 constexpr int kRestrictLanes = MFGMG_RESTRICT_LANES;   // lanes per row of the CSR transfers
 constexpr int kProlongLanes = MFGMG_PROLONG_LANES;
@@ -698,7 +698,10 @@ __global__ void k_chebx_step(int64_t n, const T* __restrict__ b, const T* __rest
 // CSR transfers, G lanes per row (rows of R hold up to 125 fine nodes, rows
 // of P up to 27 coarse ones): the lanes of a group read consecutive entries
 // (coalesced column and weight loads, G gathers in flight per row) and
-// reduce with shuffles inside the group.
+// reduce with shuffles inside the group.  Rows of P are bound by the chain row
+// pointer, entry, coarse value: two lanes with four entries in flight each
+// (leaf of the adaptive 32^3 + 2 workload, FP32: four lanes with one entry at a
+// time 265 us, two with four 168, one with eight 195).
 template <int G, typename T>
 __device__ __forceinline__ T group_sum(T v) {
 #pragma unroll
@@ -714,22 +717,33 @@ __global__ __launch_bounds__(kBlock) void k_prolong(int64_t nf, const int64_t* _
                                                     const int32_t* __restrict__ col, const W* __restrict__ w,
                                                     const T* __restrict__ xc, T* __restrict__ xf, bool add,
                                                     const uint8_t* __restrict__ cmf, const uint8_t* __restrict__ cmc) {
+  constexpr int U = 4;   // entries of a row in flight a lane
   const int sub = int(threadIdx.x) % G;
   for (int64_t f = (blockIdx.x * int64_t(blockDim.x) + threadIdx.x) / G; f < nf;
        f += int64_t(gridDim.x) * (blockDim.x / G)) {
     T a0 = T(0), a1 = T(0), a2 = T(0);
-    for (int64_t q = ptr[f] + sub; q < ptr[f + 1]; q += G) {
-      const int64_t cc = 3 * int64_t(col[q]);
-      const T ww = T(w[q]);
-      if (cmc) {
-        const unsigned m = cmc[col[q]];
-        a0 += (m & 1) ? T(0) : ww * xc[cc];
-        a1 += (m & 2) ? T(0) : ww * xc[cc + 1];
-        a2 += (m & 4) ? T(0) : ww * xc[cc + 2];
-      } else {
-        a0 += ww * xc[cc];
-        a1 += ww * xc[cc + 1];
-        a2 += ww * xc[cc + 2];
+    const int64_t end = ptr[f + 1];
+    for (int64_t q0 = ptr[f] + sub; q0 < end; q0 += U * G) {
+      int32_t c[U];
+      T ww[U], v[U][3];
+      unsigned m[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t q = min(q0 + G * u, end - 1);
+        c[u] = col[q], ww[u] = T(w[q]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const T* x = xc + 3 * int64_t(c[u]);
+        v[u][0] = x[0], v[u][1] = x[1], v[u][2] = x[2];
+        m[u] = cmc ? cmc[c[u]] : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (q0 + G * u >= end) m[u] = 7;
+        a0 += (m[u] & 1) ? T(0) : ww[u] * v[u][0];
+        a1 += (m[u] & 2) ? T(0) : ww[u] * v[u][1];
+        a2 += (m[u] & 4) ? T(0) : ww[u] * v[u][2];
       }
     }
     a0 = group_sum<G>(a0), a1 = group_sum<G>(a1), a2 = group_sum<G>(a2);
