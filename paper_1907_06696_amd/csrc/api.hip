@@ -529,7 +529,6 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
           v.outer_ent = ctx->upload(fent);
           v.fslot_f = ctx->dalloc<float>(size_t(3 * ns));
           v.fslot_d = ctx->dalloc<double>(size_t(3 * ns));
-          if (!v.fslot_f || !v.fslot_d) return ctx->set(MFGMG_ERR_NOMEM, "device allocation failed");
         }
       }
       // the same for the pressure mass blocks of the leaf ((B+1)^3 Q1 lattices)
@@ -564,7 +563,6 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
           v.pface_ptr = ctx->upload(fptr);
           v.pface_ent = ctx->upload(fent);
           v.pfslot = ctx->dalloc<double>(size_t(ns));
-          if (!v.pfslot) return ctx->set(MFGMG_ERR_NOMEM, "device allocation failed");
         }
       }
       v.single_reg = ctx->upload(sreg);
@@ -699,6 +697,7 @@ int upload_q3_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool top, const
 int upload_mesh(mfgmg_ctx* ctx) {
   if (ctx->dev_ready) return MFGMG_OK;
   HIPCHK(hipGetDevice(&ctx->device));
+  DeviceSetup setup(ctx);
   const Mesh& m = *ctx->mesh;
   const int L = m.L();
   ctx->lv.assign(size_t(L + 1), LevelDev{});
@@ -786,12 +785,13 @@ int upload_mesh(mfgmg_ctx* ctx) {
   }
   ctx->red_part = ctx->dalloc<double>(size_t(kRedPartWords));
   ctx->red_res = ctx->dalloc<double>(512);
-  HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&ctx->host_res), 512 * sizeof(double), hipHostMallocDefault));
+  if (!ctx->host_res)   // (kept when a set-up fails and is tried again)
+    HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&ctx->host_res), 512 * sizeof(double), hipHostMallocDefault));
   ctx->pmass_minv = ctx->dalloc<double>(size_t(lf.npnode));
   ctx->pmean_w = ctx->dalloc<double>(size_t(lf.npnode));
-  for (void* p : ctx->allocs)
-    if (!p) return ctx->set(MFGMG_ERR_NOMEM, "device allocation failed");
   HIPCHK(hipDeviceSynchronize());
+  const int st = setup.finish();
+  if (st) return st;
   ctx->dev_ready = true;
   return MFGMG_OK;
 }
@@ -1054,6 +1054,7 @@ int build_tail(mfgmg_ctx* ctx, hipStream_t s) {
   if (m.velocity_degree() != 2 || m.L() < 2 || m.level(2).ncell != 64) return MFGMG_OK;
   const Level &h = m.level(2), &c = m.level(1);
   if (!ctx->tail_d) {
+    DeviceSetup setup(ctx);
     const int64_t S1 = m.S() + 1;
     auto lattice = [&](const Level& lv, int64_t i) {   // lattice node of storage node i
       const int64_t step = m.S() / (2 << lv.ell), mm = (4 << (lv.ell - 1)) + 1, k = lv.key[size_t(i)];
@@ -1078,13 +1079,11 @@ int build_tail(mfgmg_ctx* ctx, hipStream_t s) {
     ctx->tail.free = ctx->upload(fd);
     ctx->tail.nfree = int(nf);
     double* Vd = ctx->dalloc<double>(nf * nf);
-    ctx->tail_f = ctx->dalloc<float>(nf * nf);
-    if (!ctx->tail.node || !ctx->tail.lattice || !ctx->tail.coarse_lattice || !ctx->tail.cell || !ctx->tail.free ||
-        !Vd || !ctx->tail_f) {
-      ctx->tail_f = nullptr;
-      return ctx->set(MFGMG_ERR_NOMEM, "device allocation failed");
-    }
+    float* Vf = ctx->dalloc<float>(nf * nf);
+    const int st = setup.finish();
+    if (st) return st;
     ctx->tail_d = Vd;
+    ctx->tail_f = Vf;
   }
   const LevelDev& d = ctx->lv[2];
   ctx->tail_c = launch_tail_columns(ctx->tail, m.noflux(), d.mu_d, d.minv_d, ctx->Ainv_d, ctx->coarse_free, d.lambda,
@@ -1376,27 +1375,31 @@ int mfgmg_set_viscosity(mfgmg_ctx* ctx, const double* mu_qp, void* stream) {
   int st = upload_mesh(ctx);
   if (st) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  double* mq = nullptr;
-  HIPCHK(hipMalloc(&mq, size_t(nq3 * nl) * sizeof(double)));
-  HIPCHK(hipMemcpyAsync(mq, mu_qp, size_t(nq3 * nl) * sizeof(double), hipMemcpyHostToDevice, s));
-  if (nq == 4) launch_harmonic_mu64(nl, mq, ctx->lv[size_t(L)].mu_d, s);
-  else launch_harmonic_mu(nl, mq, ctx->lv[size_t(L)].mu_d, s);
-  for (int ell = L - 1; ell >= 1; --ell)
-    launch_restrict_mu(ctx->lv[size_t(ell)].v.ncell, ctx->lv[size_t(ell)].mu_src, ctx->lv[size_t(ell + 1)].mu_d,
-                       ctx->lv[size_t(ell)].mu_d, s);
-  double* dtmp = nullptr;
-  HIPCHK(hipMalloc(&dtmp, size_t(3 * m.vleaf().nnode) * sizeof(double) + 64));
-  for (int ell = 1; ell <= L; ++ell) {
-    LevelDev& d = ctx->lv[size_t(ell)];
-    launch_to_float(d.v.ncell, d.mu_d, d.mu_f, s);
-    const int64_t n = 3 * d.v.nnode;
-    launch_fill(n, 0.0, dtmp, s);
-    launch_diag(d.v, ctx->khat_d, dtmp, s);
-    launch_invert_diag(d.v, dtmp, d.minv_d, d.minv_f, s);
+  {
+    struct Temp {   // given back on every way out
+      double* p = nullptr;
+      ~Temp() {
+        if (p) (void)hipFree(p);
+      }
+    } mq, dtmp;
+    HIPCHK(hipMalloc(&mq.p, size_t(nq3 * nl) * sizeof(double)));
+    HIPCHK(hipMalloc(&dtmp.p, size_t(3 * m.vleaf().nnode) * sizeof(double) + 64));
+    HIPCHK(hipMemcpyAsync(mq.p, mu_qp, size_t(nq3 * nl) * sizeof(double), hipMemcpyHostToDevice, s));
+    if (nq == 4) launch_harmonic_mu64(nl, mq.p, ctx->lv[size_t(L)].mu_d, s);
+    else launch_harmonic_mu(nl, mq.p, ctx->lv[size_t(L)].mu_d, s);
+    for (int ell = L - 1; ell >= 1; --ell)
+      launch_restrict_mu(ctx->lv[size_t(ell)].v.ncell, ctx->lv[size_t(ell)].mu_src, ctx->lv[size_t(ell + 1)].mu_d,
+                         ctx->lv[size_t(ell)].mu_d, s);
+    for (int ell = 1; ell <= L; ++ell) {
+      LevelDev& d = ctx->lv[size_t(ell)];
+      launch_to_float(d.v.ncell, d.mu_d, d.mu_f, s);
+      const int64_t n = 3 * d.v.nnode;
+      launch_fill(n, 0.0, dtmp.p, s);
+      launch_diag(d.v, ctx->khat_d, dtmp.p, s);
+      launch_invert_diag(d.v, dtmp.p, d.minv_d, d.minv_f, s);
+    }
+    HIPCHK(hipStreamSynchronize(s));
   }
-  HIPCHK(hipStreamSynchronize(s));
-  HIPCHK(hipFree(dtmp));
-  HIPCHK(hipFree(mq));
   for (int ell = 2; ell <= L; ++ell) {
     st = estimate_lambda(ctx, ell, s);
     if (st) return st;

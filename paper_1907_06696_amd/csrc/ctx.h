@@ -94,19 +94,29 @@ struct mfgmg_ctx {
     err = msg;
     return code;
   }
+  // null when the memory is not to be had; device_failed then stays set until
+  // a DeviceSetup clears it, so a set-up of many tables is checked once
   template <typename T>
   T* dalloc(size_t n) {
     void* p = nullptr;
-    if (hipMalloc(&p, std::max<size_t>(n, 1) * sizeof(T)) != hipSuccess) return nullptr;
+    if (hipMalloc(&p, std::max<size_t>(n, 1) * sizeof(T)) != hipSuccess) {
+      device_failed = true;
+      (void)hipGetLastError();   // reported here, not by the next launch
+      return nullptr;
+    }
     allocs.push_back(p);
     return static_cast<T*>(p);
   }
   template <typename T>
   T* upload(const std::vector<T>& h) {
     T* p = dalloc<T>(h.size());
-    if (p && !h.empty()) (void)hipMemcpy(p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice);
+    if (p && !h.empty() && hipMemcpy(p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice) != hipSuccess) {
+      device_failed = true;
+      (void)hipGetLastError();
+    }
     return p;
   }
+  bool device_failed = false;   // an allocation or upload failed
 };
 
 
@@ -117,6 +127,31 @@ struct mfgmg_ctx {
   } while (0)
 
 namespace mfgmg {
+
+// A group of device tables that is set up as a whole: kernels take their
+// pointers unchecked, so finish() must say that every allocation and upload
+// succeeded before any is used; what a group that did not finish allocated is
+// given back.
+class DeviceSetup {
+ public:
+  explicit DeviceSetup(mfgmg_ctx* ctx) : ctx_(ctx), first_(ctx->allocs.size()) { ctx->device_failed = false; }
+  ~DeviceSetup() {
+    for (; !finished_ && ctx_->allocs.size() > first_; ctx_->allocs.pop_back()) (void)hipFree(ctx_->allocs.back());
+  }
+  DeviceSetup(const DeviceSetup&) = delete;
+  DeviceSetup& operator=(const DeviceSetup&) = delete;
+  int finish() {
+    if (ctx_->device_failed) return ctx_->set(MFGMG_ERR_NOMEM, "device allocation failed");
+    finished_ = true;
+    return MFGMG_OK;
+  }
+
+ private:
+  mfgmg_ctx* ctx_;
+  size_t first_;
+  bool finished_ = false;
+};
+
 namespace detail {
 
 int upload_mesh(mfgmg_ctx* ctx);

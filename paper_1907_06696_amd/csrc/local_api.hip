@@ -171,6 +171,7 @@ int local_setup(mfgmg_ctx* ctx, hipStream_t s) {
   const int L = m.L(), base = m.local_base();
   if (base >= L) return MFGMG_OK;   // uniform leaf: the local cycle is the global one
   if (!ctx->ls_ready) {
+    DeviceSetup setup(ctx);
     ctx->ls.assign(size_t(L + 1), LocalDev{});
     for (int ell = base + 1; ell <= L; ++ell) {
       const LocalLevel& h = m.local_level(ell);
@@ -194,15 +195,12 @@ int local_setup(mfgmg_ctx* ctx, hipStream_t s) {
       const size_t n = size_t(3 * h.mesh.nnode);
       l.ext[0][0] = ctx->dalloc<float>(n), l.ext[0][1] = ctx->dalloc<float>(n);
       l.ext[1][0] = ctx->dalloc<double>(n), l.ext[1][1] = ctx->dalloc<double>(n);
-      if (!l.kind || !l.gc_cell || !l.ext[0][0] || !l.ext[0][1] || !l.ext[1][0] || !l.ext[1][1] ||
-          (l.ncopy && (!l.copy_leaf || !l.copy_node)))
-        return ctx->set(MFGMG_ERR_NOMEM, "device allocation failed");
     }
     ctx->ls_base_leaf = ctx->upload(m.local_base_copy_leaf());
     ctx->ls_base_node = ctx->upload(m.local_base_copy_node());
     ctx->ls_base_ncopy = int64_t(m.local_base_copy_leaf().size());
-    if (ctx->ls_base_ncopy && (!ctx->ls_base_leaf || !ctx->ls_base_node))
-      return ctx->set(MFGMG_ERR_NOMEM, "device allocation failed");
+    const int st = setup.finish();
+    if (st) return st;
     ctx->ls_ready = true;
   }
   if (!ctx->ls_mu_ready) {

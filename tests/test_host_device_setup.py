@@ -1,0 +1,127 @@
+"""What the library's device set-up does when a device allocation or an upload
+fails: the call returns an error, gives back what it had allocated, and works
+when it is called again.  Kernels take the set-up's pointers unchecked, so a
+failure that went unseen would be a GPU fault.  Runs on the CPU: the HIP
+runtime calls of libmfgmg.so are those of tests/native/hip_host.cpp (host
+memory, kernels never run), in a process of its own."""
+import ctypes as C
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+# base level, boundary condition, element and refined cells: uniform levels,
+# levels run as a grid through maps, blocks and hanging nodes, lattice levels
+CASES = {"uniform": (3, "dirichlet", 1, ()), "noflux": (3, "noflux", 1, ()),
+         "adaptive": (3, "dirichlet", 1, ((0, 0, 0), (5, 2, 7))), "q3": (3, "dirichlet", 2, ())}
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    so = str(tmp_path_factory.mktemp("hip_host") / "hip_host.so")
+    r = subprocess.run([gxx, "-std=c++17", "-O1", "-shared", "-fPIC",
+                        os.path.join(ROOT, "tests", "native", "hip_host.cpp"), "-o", so], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return so
+
+
+def run(stub, what, case):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), stub, what, case], capture_output=True, text=True,
+                       timeout=300, cwd=ROOT)
+    assert r.returncode == 0, f"{what} {case}: exit {r.returncode}\n{r.stdout}\n{r.stderr}"
+
+
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_failed_allocation_is_reported(stub, case):
+    run(stub, "allocation", case)
+
+
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_failed_upload_is_reported(stub, case):
+    run(stub, "upload", case)
+
+
+def test_failed_allocation_of_local_levels_is_reported(stub):
+    run(stub, "local", "adaptive")
+
+
+# ---------------------------------------------------- the process with the stub
+
+class Child:
+    def __init__(self, stub, case):
+        import numpy as np
+        self.np = np
+        self.hip = C.CDLL(stub, mode=C.RTLD_GLOBAL)   # before the library: found first
+        for f in ("stub_mallocs", "stub_copies", "stub_held"):
+            getattr(self.hip, f).restype = C.c_int64
+        for f in ("stub_fail_malloc", "stub_fail_copy"):
+            getattr(self.hip, f).argtypes = [C.c_int64]
+        sys.path.insert(0, ROOT)
+        from paper_1907_06696_amd import mfgmg
+        self.m = mfgmg
+        self.spec = CASES[case]
+
+    def solver(self):
+        base, bc, k, refined = self.spec
+        s = self.m.Solver(base)
+        s.set_boundary(bc)
+        s.set_element(k)
+        if refined:
+            s.refine(self.np.array([(base,) + c for c in refined], self.np.int32), 1)
+        s.finalize_mesh()
+        self.mu = self.np.ones(s.leaf_quadrature_points().shape[:2])
+        return s
+
+    def set_viscosity(self, s):
+        return s.lib.mfgmg_set_viscosity(s.h, self.mu.ctypes.data, None)
+
+    def every_failure(self, arm, counter, prepare, call):
+        """Counts the operations of a call that succeeds, then has each of them fail in turn."""
+        hip, m = self.hip, self.m
+        s = prepare()
+        arm(0)
+        assert call(s) == m.OK
+        count, kept = counter(), hip.stub_held()
+        s.close()
+        assert count > 0 and hip.stub_held() == 0
+        for n in range(1, count + 1):
+            s = prepare()
+            arm(n)
+            code = call(s)
+            arm(0)
+            assert code in (m.ERR_NOMEM, m.ERR_HIP), f"operation {n} of {count} failed and the call returned {code}"
+            # called again, it finds nothing half done and nothing kept twice
+            assert call(s) == m.OK and hip.stub_held() == kept, f"after failure {n} of {count}"
+            s.close()
+            assert hip.stub_held() == 0
+
+    def allocation(self):
+        self.every_failure(self.hip.stub_fail_malloc, self.hip.stub_mallocs, self.solver, self.set_viscosity)
+
+    def upload(self):
+        self.every_failure(self.hip.stub_fail_copy, self.hip.stub_copies, self.solver, self.set_viscosity)
+
+    def ready(self):
+        s = self.solver()
+        assert self.set_viscosity(s) == self.m.OK
+        return s
+
+    def vcycle_local(self, s):
+        b, x = (self.np.zeros(s.info()["n_u"][s.info()["L"]]) for _ in range(2))
+        return s.lib.mfgmg_vcycle_local(s.h, self.m.FP64, b.ctypes.data, x.ctypes.data, None)
+
+    def local(self):
+        self.every_failure(self.hip.stub_fail_malloc, self.hip.stub_mallocs, self.ready, self.vcycle_local)
+        self.every_failure(self.hip.stub_fail_copy, self.hip.stub_copies, self.ready, self.vcycle_local)
+
+
+if __name__ == "__main__":
+    child = Child(sys.argv[1], sys.argv[3])
+    getattr(child, sys.argv[2])()
