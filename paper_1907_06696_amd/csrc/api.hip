@@ -1362,7 +1362,7 @@ int mfgmg_leaf_quadrature_points(const mfgmg_ctx* ctx, double* xyz) {
   return MFGMG_OK;
 }
 
-int mfgmg_set_viscosity(mfgmg_ctx* ctx, const double* mu_qp, void* stream) {
+int mfgmg_set_viscosity(mfgmg_ctx* ctx, const double* mu_qp, void* stream) try {
   if (!ctx || !mu_qp) return MFGMG_ERR_INVALID;
   if (!ctx->mesh->finalized()) return ctx->set(MFGMG_ERR_STATE, "finalize the mesh first");
   const Mesh& m = *ctx->mesh;
@@ -1376,12 +1376,7 @@ int mfgmg_set_viscosity(mfgmg_ctx* ctx, const double* mu_qp, void* stream) {
   if (st) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   {
-    struct Temp {   // given back on every way out
-      double* p = nullptr;
-      ~Temp() {
-        if (p) (void)hipFree(p);
-      }
-    } mq, dtmp;
+    DeviceTemp mq, dtmp;
     HIPCHK(hipMalloc(&mq.p, size_t(nq3 * nl) * sizeof(double)));
     HIPCHK(hipMalloc(&dtmp.p, size_t(3 * m.vleaf().nnode) * sizeof(double) + 64));
     HIPCHK(hipMemcpyAsync(mq.p, mu_qp, size_t(nq3 * nl) * sizeof(double), hipMemcpyHostToDevice, s));
@@ -1413,6 +1408,8 @@ int mfgmg_set_viscosity(mfgmg_ctx* ctx, const double* mu_qp, void* stream) {
   ctx->ls_mu_ready = false;   // the local levels take their viscosity on first use
   ctx->mu_ready = true;
   return MFGMG_OK;
+} catch (...) {
+  return host_memory_failed(ctx);
 }
 
 int mfgmg_cell_viscosity(const mfgmg_ctx* ctx, int32_t level, double* mu) {
@@ -1561,7 +1558,7 @@ int mfgmg_coarse_solve(mfgmg_ctx* ctx, mfgmg_prec prec, const void* b, void* x, 
   return MFGMG_OK;
 }
 
-int mfgmg_assemble_rhs(mfgmg_ctx* ctx, const double* f_qp, double* rhs_u, void* stream) {
+int mfgmg_assemble_rhs(mfgmg_ctx* ctx, const double* f_qp, double* rhs_u, void* stream) try {
   if (!ctx || !f_qp || !rhs_u) return MFGMG_ERR_INVALID;
   if (!ctx->mesh->finalized()) return ctx->set(MFGMG_ERR_STATE, "finalize the mesh first");
   int st = upload_mesh(ctx);
@@ -1570,13 +1567,14 @@ int mfgmg_assemble_rhs(mfgmg_ctx* ctx, const double* f_qp, double* rhs_u, void* 
   const DevLevel& v = ctx->lv[size_t(ctx->mesh->L())].v;
   const int nq = ctx->mesh->quad_points();
   const size_t nf = size_t(3 * nq * nq * nq) * size_t(v.ncell);
-  double* fd = nullptr;
-  HIPCHK(hipMalloc(&fd, nf * sizeof(double)));
-  HIPCHK(hipMemcpyAsync(fd, f_qp, nf * sizeof(double), hipMemcpyHostToDevice, s));
-  launch_rhs(v, fd, rhs_u, s);
+  DeviceTemp fd;
+  HIPCHK(hipMalloc(&fd.p, nf * sizeof(double)));
+  HIPCHK(hipMemcpyAsync(fd.p, f_qp, nf * sizeof(double), hipMemcpyHostToDevice, s));
+  launch_rhs(v, fd.p, rhs_u, s);
   HIPCHK(hipStreamSynchronize(s));
-  HIPCHK(hipFree(fd));
   return MFGMG_OK;
+} catch (...) {
+  return host_memory_failed(ctx);
 }
 
 int mfgmg_apply_div(mfgmg_ctx* ctx, const double* u, double* p_out, void* stream) {
@@ -1627,7 +1625,7 @@ int mfgmg_default_opts(mfgmg_solve_opts* o) {
 }
 
 int mfgmg_solve_stokes(mfgmg_ctx* ctx, const double* rhs_u, const double* rhs_p, double* u_out, double* p_out,
-                       const mfgmg_solve_opts* opts, mfgmg_solve_stats* stats, void* stream) {
+                       const mfgmg_solve_opts* opts, mfgmg_solve_stats* stats, void* stream) try {
   if (!ctx || !rhs_u || !u_out || !p_out) return MFGMG_ERR_INVALID;
   if (!ctx->mu_ready) return ctx->set(MFGMG_ERR_STATE, "set_viscosity first");
   mfgmg_solve_opts o;
@@ -2148,6 +2146,8 @@ int mfgmg_solve_stokes(mfgmg_ctx* ctx, const double* rhs_u, const double* rhs_p,
   }
   if (!conv) return ctx->set(MFGMG_ERR_NOCONV, bad ? "NaN or Inf in the solve" : "tolerance not reached");
   return MFGMG_OK;
+} catch (...) {
+  return host_memory_failed(ctx);
 }
 
 const char* mfgmg_last_error(const mfgmg_ctx* ctx) { return ctx ? ctx->err.c_str() : g_last_error.c_str(); }

@@ -98,14 +98,14 @@ struct mfgmg_ctx {
   // a DeviceSetup clears it, so a set-up of many tables is checked once
   template <typename T>
   T* dalloc(size_t n) {
-    void* p = nullptr;
-    if (hipMalloc(&p, std::max<size_t>(n, 1) * sizeof(T)) != hipSuccess) {
+    allocs.push_back(nullptr);   // may throw, so before there is something to lose
+    if (hipMalloc(&allocs.back(), std::max<size_t>(n, 1) * sizeof(T)) != hipSuccess) {
+      allocs.pop_back();
       device_failed = true;
       (void)hipGetLastError();   // reported here, not by the next launch
       return nullptr;
     }
-    allocs.push_back(p);
-    return static_cast<T*>(p);
+    return static_cast<T*>(allocs.back());
   }
   template <typename T>
   T* upload(const std::vector<T>& h) {
@@ -127,6 +127,24 @@ struct mfgmg_ctx {
   } while (0)
 
 namespace mfgmg {
+
+// What a C entry that allocates host memory returns in place of an exception
+// (the message fits a std::string without an allocation).
+inline int host_memory_failed(mfgmg_ctx* ctx) noexcept {
+  ctx->err = "out of memory";
+  return MFGMG_ERR_NOMEM;
+}
+
+// Device array of one call, freed on every way out of it.
+struct DeviceTemp {
+  double* p = nullptr;
+  DeviceTemp() = default;
+  DeviceTemp(const DeviceTemp&) = delete;
+  DeviceTemp& operator=(const DeviceTemp&) = delete;
+  ~DeviceTemp() {
+    if (p) (void)hipFree(p);
+  }
+};
 
 // A group of device tables that is set up as a whole: kernels take their
 // pointers unchecked, so finish() must say that every allocation and upload

@@ -206,23 +206,19 @@ int local_setup(mfgmg_ctx* ctx, hipStream_t s) {
   if (!ctx->ls_mu_ready) {
     int64_t nmax = 0;
     for (int ell = base + 1; ell <= L; ++ell) nmax = std::max(nmax, 3 * ctx->ls[size_t(ell)].a.v.nnode);
-    double* dtmp = nullptr;
-    HIPCHK(hipMalloc(&dtmp, size_t(nmax) * sizeof(double)));
+    DeviceTemp dtmp;
+    HIPCHK(hipMalloc(&dtmp.p, size_t(nmax) * sizeof(double)));
     for (int ell = base + 1; ell <= L; ++ell) {
       LocalDev& l = ctx->ls[size_t(ell)];
       const int64_t nc = l.a.v.ncell;
       k_ls_gather_mu<<<ls_grid(nc), kLsBlock, 0, s>>>(nc, l.gc_cell, ctx->lv[size_t(ell)].mu_d, l.a.mu_d, l.a.mu_f);
-      launch_fill(3 * l.a.v.nnode, 0.0, dtmp, s);
-      launch_diag(l.a.v, ctx->khat_d, dtmp, s);
-      launch_invert_diag(l.a.v, dtmp, l.a.minv_d, l.a.minv_f, s);
+      launch_fill(3 * l.a.v.nnode, 0.0, dtmp.p, s);
+      launch_diag(l.a.v, ctx->khat_d, dtmp.p, s);
+      launch_invert_diag(l.a.v, dtmp.p, l.a.minv_d, l.a.minv_f, s);
       const int st = lanczos_on(ctx, l.a, m.local_level(ell).mesh, l.a.minv_d, &l.a.lambda, s);
-      if (st) {
-        (void)hipFree(dtmp);
-        return st;
-      }
+      if (st) return st;
     }
     HIPCHK(hipStreamSynchronize(s));
-    HIPCHK(hipFree(dtmp));
     ctx->ls_mu_ready = true;
   }
   return MFGMG_OK;
@@ -324,7 +320,7 @@ int mfgmg_local_transfer(const mfgmg_ctx* ctx, int32_t level, int64_t* nnz, int6
   return MFGMG_OK;
 }
 
-int mfgmg_vcycle_local(mfgmg_ctx* ctx, mfgmg_prec prec, const void* rhs, void* x, void* stream) {
+int mfgmg_vcycle_local(mfgmg_ctx* ctx, mfgmg_prec prec, const void* rhs, void* x, void* stream) try {
   if (!ctx || !rhs || !x || rhs == x || (prec != MFGMG_FP32 && prec != MFGMG_FP64)) return MFGMG_ERR_INVALID;
   if (!ctx->mu_ready) return ctx->set(MFGMG_ERR_STATE, "set_viscosity first");
   if (ctx->mesh->noflux() || ctx->mesh->velocity_degree() != 2)
@@ -338,6 +334,8 @@ int mfgmg_vcycle_local(mfgmg_ctx* ctx, mfgmg_prec prec, const void* rhs, void* x
     local_vcycle<float>(ctx, static_cast<const float*>(rhs), static_cast<float*>(x), s);
   HIPCHK(hipGetLastError());
   return MFGMG_OK;
+} catch (...) {
+  return host_memory_failed(ctx);
 }
 
 }  // extern "C"

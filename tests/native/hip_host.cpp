@@ -8,9 +8,11 @@
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 
 namespace {
 int64_t mallocs = 0, fail_malloc = 0, copies = 0, fail_copy = 0, held = 0;
+int64_t news = 0, fail_new = 0;
 constexpr int kOutOfMemory = 2, kInvalid = 1;
 
 int copy(void* dst, const void* src, size_t n, int kind) {
@@ -25,11 +27,14 @@ int copy(void* dst, const void* src, size_t n, int kind) {
 }  // namespace
 
 extern "C" {
-// the n-th call from now fails (0: none): hipMalloc, synchronous hipMemcpy
+// the n-th call from now fails (0: none): hipMalloc, synchronous hipMemcpy,
+// operator new of the library's host code (from the n-th on)
 void stub_fail_malloc(int64_t n) { mallocs = 0, fail_malloc = n; }
 void stub_fail_copy(int64_t n) { copies = 0, fail_copy = n; }
+void stub_fail_new(int64_t n) { news = 0, fail_new = n; }
 int64_t stub_mallocs() { return mallocs; }
 int64_t stub_copies() { return copies; }
+int64_t stub_news() { return news; }
 int64_t stub_held() { return held; }   // device allocations not freed
 
 int hipMalloc(void** p, size_t n) {
@@ -96,3 +101,12 @@ void __hipRegisterFunction(...) {}
 void __hipRegisterVar(...) {}
 void __hipUnregisterFatBinary(void*) {}
 }
+
+void* operator new(size_t n) {
+  ++news;
+  if (fail_new && news >= fail_new) throw std::bad_alloc();
+  if (void* p = std::malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }

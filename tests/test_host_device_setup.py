@@ -51,6 +51,11 @@ def test_failed_upload_is_reported(stub, case):
 def test_failed_allocation_of_local_levels_is_reported(stub):
     run(stub, "local", "adaptive")
 
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_host_memory_running_out_is_reported(stub, case):
+    """No C++ exception leaves the C entries that set up device data."""
+    run(stub, "host_memory", case)
+
 
 # ---------------------------------------------------- the process with the stub
 
@@ -59,9 +64,9 @@ class Child:
         import numpy as np
         self.np = np
         self.hip = C.CDLL(stub, mode=C.RTLD_GLOBAL)   # before the library: found first
-        for f in ("stub_mallocs", "stub_copies", "stub_held"):
+        for f in ("stub_mallocs", "stub_copies", "stub_news", "stub_held"):
             getattr(self.hip, f).restype = C.c_int64
-        for f in ("stub_fail_malloc", "stub_fail_copy"):
+        for f in ("stub_fail_malloc", "stub_fail_copy", "stub_fail_new"):
             getattr(self.hip, f).argtypes = [C.c_int64]
         sys.path.insert(0, ROOT)
         from paper_1907_06696_amd import mfgmg
@@ -107,6 +112,33 @@ class Child:
 
     def upload(self):
         self.every_failure(self.hip.stub_fail_copy, self.hip.stub_copies, self.solver, self.set_viscosity)
+
+    def host_memory(self):
+        np, hip, m = self.np, self.hip, self.m
+        f = np.zeros(self.solver().leaf_quadrature_points().shape)
+
+        def rhs(s):
+            b = np.zeros(s.info()["n_u"][s.info()["L"]])
+            return s.lib.mfgmg_assemble_rhs(s.h, f.ctypes.data, b.ctypes.data, None)
+
+        calls = [(self.solver, self.set_viscosity), (self.solver, rhs)]
+        if self.spec[3]:
+            calls.append((self.ready, self.vcycle_local))
+        for prepare, call in calls:
+            s = prepare()
+            hip.stub_fail_new(0)
+            assert call(s) == m.OK
+            count = hip.stub_news()
+            s.close()
+            for n in sorted({1, 2, 3, count, *(max(1, int(count * q / 40)) for q in range(40))}):
+                s = prepare()
+                hip.stub_fail_new(n)
+                code = call(s)
+                hip.stub_fail_new(0)
+                assert code == m.ERR_NOMEM, f"host allocation {n} of {count} failed and the call returned {code}"
+                assert call(s) == m.OK
+                s.close()
+                assert hip.stub_held() == 0
 
     def ready(self):
         s = self.solver()
