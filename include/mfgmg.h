@@ -181,7 +181,9 @@ int mfgmg_leaf_quadrature_points(const mfgmg_ctx* ctx, double* xyz_host);
  * coarser level (Sec. 2.3); inverse diagonals of every level operator;
  * Chebyshev eigenvalue estimates; coarse factorisation.  Allocates the
  * library's device memory on first use.  Synchronises `stream`.
- * Errors: ERR_INVALID for non-positive or non-finite values. */
+ * Errors: ERR_INVALID for non-positive or non-finite values; ERR_NOMEM,
+ * ERR_HIP, ERR_NOCONV.  One that comes after the levels began to change leaves
+ * no viscosity set (ERR_STATE from the calls that need it). */
 int mfgmg_set_viscosity(mfgmg_ctx* ctx, const double* mu_qp_host, void* stream);
 
 /* Cell viscosities of a level after averaging: [n_cells[level]] (host copy). */

@@ -1379,6 +1379,7 @@ int mfgmg_set_viscosity(mfgmg_ctx* ctx, const double* mu_qp, void* stream) try {
     DeviceTemp mq, dtmp;
     HIPCHK(hipMalloc(&mq.p, size_t(nq3 * nl) * sizeof(double)));
     HIPCHK(hipMalloc(&dtmp.p, size_t(3 * m.vleaf().nnode) * sizeof(double) + 64));
+    ctx->mu_ready = false;   // until all that depends on the viscosity has followed
     HIPCHK(hipMemcpyAsync(mq.p, mu_qp, size_t(nq3 * nl) * sizeof(double), hipMemcpyHostToDevice, s));
     if (nq == 4) launch_harmonic_mu64(nl, mq.p, ctx->lv[size_t(L)].mu_d, s);
     else launch_harmonic_mu(nl, mq.p, ctx->lv[size_t(L)].mu_d, s);

@@ -56,6 +56,13 @@ def test_host_memory_running_out_is_reported(stub, case):
     """No C++ exception leaves the C entries that set up device data."""
     run(stub, "host_memory", case)
 
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_viscosity_that_failed_half_way_is_not_used(stub, case):
+    """A later mfgmg_set_viscosity that fails after it began to change the levels leaves no mix of two viscosities
+    behind (the 4^3 level's matrix and the coarse factor of the old one under the operators of the new one): calls
+    that need it say that none is set.  One that fails before leaves the old one in use."""
+    run(stub, "half_way", case)
+
 
 # ---------------------------------------------------- the process with the stub
 
@@ -139,6 +146,33 @@ class Child:
                 assert call(s) == m.OK
                 s.close()
                 assert hip.stub_held() == 0
+
+    def half_way(self):
+        np, hip, m = self.np, self.hip, self.m
+        s = self.ready()
+        L = s.info()["L"]
+        x, y = (np.zeros(s.info()["n_u"][L]) for _ in range(2))
+
+        def vmult():
+            return s.lib.mfgmg_vmult(s.h, L, m.FP64, x.ctypes.data, y.ctypes.data, None)
+
+        hip.stub_fail_new(0)
+        assert self.set_viscosity(s) == m.OK
+        count = hip.stub_news()
+        for n in sorted({1, count // 2, count}):   # host tables of the eigenvalue estimates to the pressure's
+            hip.stub_fail_new(n)
+            assert self.set_viscosity(s) == m.ERR_NOMEM
+            hip.stub_fail_new(0)
+            assert vmult() == m.ERR_STATE, f"host allocation {n} of {count}"
+            assert self.set_viscosity(s) == m.OK and vmult() == m.OK
+        for n in (1, 2):   # its temporary arrays, before it changes anything
+            hip.stub_fail_malloc(n)
+            assert self.set_viscosity(s) != m.OK
+            hip.stub_fail_malloc(0)
+            assert vmult() == m.OK
+        self.mu[0, 0] = -1.0
+        assert self.set_viscosity(s) == m.ERR_INVALID and vmult() == m.OK
+        s.close()
 
     def ready(self):
         s = self.solver()
