@@ -154,10 +154,11 @@ _DTYPE_NAME = {FP32: "float32", FP64: "float64"}
 
 
 def _torch_cuda():
-    """torch.cuda once the program has initialised it, else None: before that
-    there is no GPU tensor and the current stream is the default one."""
+    """torch.cuda where there is a GPU that it can use, else None.  Once it is
+    initialised nothing else is asked; before, and in a forked child, torch's
+    own checks apply (it refuses a child of a process that used the GPU)."""
     torch = sys.modules.get("torch")
-    if torch is not None and torch.cuda.is_initialized():
+    if torch is not None and (torch.cuda.is_initialized() or torch.cuda.is_available()):
         return torch.cuda
     return None
 
@@ -221,7 +222,8 @@ def current_stream():
     cuda = _torch_cuda()
     if cuda is None:
         return C.c_void_p(0)
-    # the handle alone where torch offers it (0.1 us; a Stream object takes 3 us)
+    # the handle alone where torch offers it (0.1 us; a Stream object takes 3
+    # us); the current device is asked first, which initialises torch
     raw = getattr(sys.modules["torch"]._C, "_cuda_getCurrentRawStream", None)
     return C.c_void_p(raw(cuda.current_device()) if raw is not None else cuda.current_stream().cuda_stream)
 
