@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <memory>
 #include <string>
 #include <vector>
@@ -206,12 +207,35 @@ thread_local std::string g_last_error;
 
 double splitmix_pm1(uint64_t seed, uint64_t counter) { return splitmix_value(seed, counter); }
 
+// Slots grouped by node, from (node, slot) pairs in increasing slot: nodes in
+// order, those with slots or, given `take`, those it names (which include them);
+// the slots of node[i] are ent[ptr[i] .. ptr[i + 1]).  Counted, not sorted: two
+// sorts of every pair were a tenth of an adaptive mesh's set-up.
+struct NodeSlots {
+  std::vector<int32_t> node, ptr{0}, ent;
+  NodeSlots(const std::vector<std::pair<int32_t, int32_t>>& pairs, int64_t nnode,
+            const std::function<bool(int64_t)>& take = nullptr)
+      : ent(pairs.size()) {
+    std::vector<int32_t> end(static_cast<size_t>(nnode + 1), 0);
+    for (const auto& e : pairs) ++end[size_t(e.first) + 1];
+    for (int64_t i = 0; i < nnode; ++i) {
+      if (take ? take(i) : end[size_t(i + 1)] > 0) {
+        node.push_back(int32_t(i));
+        ptr.push_back(end[size_t(i)] + end[size_t(i + 1)]);
+      }
+      end[size_t(i + 1)] += end[size_t(i)];
+    }
+    for (const auto& e : pairs) ent[size_t(end[size_t(e.first)]++)] = e.second;
+  }
+};
 
 // Device data of one level from its host mesh: node lists, cell tables and
-// the operator's block partition (non-uniform levels; the leaf also keeps
-// its cell tables and pressure blocks), transfers from the level below,
-// brick halo slots (uniform levels), viscosity, inverse diagonal and work
-// vectors (work = false: the operator data only).
+// the operator's block partition (non-uniform levels; the leaf with its pressure
+// blocks), transfers from the level below, brick halo slots (uniform levels),
+// viscosity, inverse diagonal and work vectors (work = false: the operator data
+// only).  Tables that no kernel of a level reads are not built: on a uniform leaf
+// they were three quarters of the first set_viscosity (64^3: 257 ms, 51 without;
+// 32^3: 34, 10), on levels run as a grid a quarter (32^3 leaf: 52, 37).
 int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool top, bool transfers, bool work) {
   DevLevel& v = d.v;
   v.ell = h.ell;
@@ -252,7 +276,7 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
         if (x >= 0) x |= int32_t(h.fixmask[size_t(x)]) << kSlotFixShift;
     return sl;
   };
-  if (!h.uniform || leaf) {   // the leaf keeps cell tables for the pressure operators
+  if (!h.uniform) {
     std::vector<int32_t> slots(static_cast<size_t>(27 * h.ncell));
     std::vector<int8_t> clev(static_cast<size_t>(h.ncell));
     std::vector<int32_t> reg, hang;
@@ -280,7 +304,8 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
     v.hang_cells = ctx->upload(hang);
     v.n_hang_cells = int64_t(hang.size());
     // operator partition into 4^3 blocks, then 2^3 blocks, then single cells
-    {
+    // (a grid level's velocity operator goes without, its pressure operators not)
+    if (!v.grid_edge || leaf) {
       std::unordered_map<uint64_t, int32_t> at;
       at.reserve(size_t(h.ncell));
       auto code = [](int l, int64_t i, int64_t j, int64_t k) {
@@ -404,14 +429,14 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
       std::vector<int32_t> sreg, shang;
       make_blocks(4, b4);
       make_blocks(2, b2);
-      Blocks b1;   // the cells in no block that have no hanging node
+      Blocks b1;   // velocity operator: the cells in no block that have no hanging node
       std::vector<int32_t> cs1(27);
       for (int64_t c = 0; c < h.ncell; ++c) {
         if (used[size_t(c)]) continue;
         bool hh = false;
         for (int a = 0; a < 27; ++a) hh = hh || slots[size_t(27 * c + a)] < -1;
         (hh ? shang : sreg).push_back(int32_t(c));
-        if (hh) continue;
+        if (hh || v.grid_edge) continue;
         b1.cells.push_back(int32_t(c));
         for (int a = 0; a < 27; ++a) cs1[size_t(place(1, a % 3, a / 3 % 3, a / 9))] = slots[size_t(27 * c + a)];
         b1.slots.insert(b1.slots.end(), cs1.begin(), cs1.end());
@@ -491,44 +516,27 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
         };
         const int64_t s2 = faces(b4, 4, 0);
         const int64_t s1 = faces(b2, 2, s2);
-        std::vector<int32_t> fnode, fptr, fent;
-        // node by node (all: every free node but the blocks' inner points)
-        auto group = [&](bool all) {
-          std::sort(nf.begin(), nf.end());
-          fnode.clear();
-          fptr.assign(1, 0);
-          fent.clear();
-          size_t q = 0;
-          auto take = [&](int32_t nd) {
-            fnode.push_back(nd);
-            for (; q < nf.size() && nf[q].first == nd; ++q) fent.push_back(nf[q].second);
-            fptr.push_back(int32_t(fent.size()));
-          };
-          if (all) {
-            for (int64_t i = 0; i < h.nnode; ++i)
-              if (h.ntype[size_t(i)] == NODE_FREE && !is_inner[size_t(i)]) take(int32_t(i));
-          } else {
-            while (q < nf.size()) take(nf[q].first);
-          }
-        };
-        group(false);
+        const NodeSlots face(nf, h.nnode);
         v.fslot_blk2 = s2;
         v.fslot_blk1 = s1;
-        v.n_face = int64_t(fnode.size());
+        v.n_face = int64_t(face.node.size());
         if (v.n_face) {
-          v.face_node = ctx->upload(fnode);
-          v.face_ptr = ctx->upload(fptr);
-          v.face_ent = ctx->upload(fent);
+          v.face_node = ctx->upload(face.node);
+          v.face_ptr = ctx->upload(face.ptr);
+          v.face_ent = ctx->upload(face.ent);
         }
         const int64_t ns = faces(b1, 1, s1);
-        group(true);
-        v.n_outer = int64_t(fnode.size());
-        if (v.n_outer) {
-          v.outer_node = ctx->upload(fnode);
-          v.outer_ptr = ctx->upload(fptr);
-          v.outer_ent = ctx->upload(fent);
+        if (ns) {
           v.fslot_f = ctx->dalloc<float>(size_t(3 * ns));
           v.fslot_d = ctx->dalloc<double>(size_t(3 * ns));
+        }
+        if (!v.grid_edge) {   // every free node but the blocks' inner points
+          const NodeSlots outer(nf, h.nnode,
+                                [&](int64_t i) { return h.ntype[size_t(i)] == NODE_FREE && !is_inner[size_t(i)]; });
+          v.n_outer = int64_t(outer.node.size());
+          v.outer_node = ctx->upload(outer.node);
+          v.outer_ptr = ctx->upload(outer.ptr);
+          v.outer_ent = ctx->upload(outer.ent);
         }
       }
       // the same for the pressure mass blocks of the leaf ((B+1)^3 Q1 lattices)
@@ -548,20 +556,13 @@ int upload_level(mfgmg_ctx* ctx, const Level& h, LevelDev& d, bool leaf, bool to
         };
         const int64_t s2 = faces(b4, 4, 0);
         const int64_t ns = faces(b2, 2, s2);
-        std::sort(nf.begin(), nf.end());
-        std::vector<int32_t> fnode, fptr{0}, fent;
-        for (size_t i = 0; i < nf.size(); ++i) {
-          if (i && nf[i].first != nf[i - 1].first) fptr.push_back(int32_t(fent.size()));
-          if (i == 0 || nf[i].first != nf[i - 1].first) fnode.push_back(nf[i].first);
-          fent.push_back(nf[i].second);
-        }
-        if (!nf.empty()) fptr.push_back(int32_t(fent.size()));
+        const NodeSlots face(nf, h.npnode);
         v.pfslot_blk2 = s2;
-        v.n_pface = int64_t(fnode.size());
+        v.n_pface = int64_t(face.node.size());
         if (v.n_pface) {
-          v.pface_node = ctx->upload(fnode);
-          v.pface_ptr = ctx->upload(fptr);
-          v.pface_ent = ctx->upload(fent);
+          v.pface_node = ctx->upload(face.node);
+          v.pface_ptr = ctx->upload(face.ptr);
+          v.pface_ent = ctx->upload(face.ent);
           v.pfslot = ctx->dalloc<double>(size_t(ns));
         }
       }
@@ -742,14 +743,16 @@ int upload_mesh(mfgmg_ctx* ctx) {
   // pressure on the leaf
   const Level& lf = m.vleaf();
   if (m.velocity_degree() == 2) {
-    std::vector<int32_t> ps(static_cast<size_t>(8 * lf.ncell));
-    for (int64_t c = 0; c < lf.ncell; ++c)
-      for (int i = 0; i < 8; ++i) {
-        const int32_t n = lf.cell_pnodes[size_t(8 * c + i)];
-        ps[size_t(8 * c + i)] = lf.ptype[size_t(n)] == NODE_HANGING ? -(2 + lf.phang_index[size_t(n)]) : n;
-      }
     ctx->pres.np = lf.npnode;
-    ctx->pres.pslots = ctx->upload(ps);
+    if (!lf.uniform) {
+      std::vector<int32_t> ps(static_cast<size_t>(8 * lf.ncell));
+      for (int64_t c = 0; c < lf.ncell; ++c)
+        for (int i = 0; i < 8; ++i) {
+          const int32_t n = lf.cell_pnodes[size_t(8 * c + i)];
+          ps[size_t(8 * c + i)] = lf.ptype[size_t(n)] == NODE_HANGING ? -(2 + lf.phang_index[size_t(n)]) : n;
+        }
+      ctx->pres.pslots = ctx->upload(ps);
+    }
     ctx->pres.hptr = ctx->upload(lf.phang.ptr);
     ctx->pres.hmaster = ctx->upload(lf.phang.master);
     ctx->pres.hw = ctx->upload(lf.phang.weight);

@@ -104,7 +104,8 @@ struct DevLevel {
   const int32_t* reg_cells = nullptr;   // the other cells
   int64_t n_reg_cells = 0;
   // operator partition: blocks of 4^3 and 2^3 same-level cells, and the
-  // remaining single cells with and without hanging nodes
+  // remaining single cells with and without hanging nodes (grid levels: on the
+  // leaf, for the pressure operators)
   DevBlocks blk4, blk2, blk1;   // blk1: the single_reg cells one by one (velocity tables only)
   const int32_t* single_reg = nullptr;
   int64_t n_single_reg = 0;
@@ -292,7 +293,7 @@ void launch_mul(int64_t n, const double* a, const double* b, double* y, hipStrea
 // leaf pressure operators (FP64)
 struct DevPressure {
   int64_t np = 0;
-  const int32_t* pslots = nullptr;   // [8*ncell]: node >= 0 free, -(2+h) hanging row h
+  const int32_t* pslots = nullptr;   // non-uniform leaf, [8*ncell]: node >= 0 free, -(2+h) hanging row h
   const int64_t* hptr = nullptr;
   const int32_t* hmaster = nullptr;
   const double* hw = nullptr;

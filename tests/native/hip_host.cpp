@@ -11,7 +11,7 @@
 #include <new>
 
 namespace {
-int64_t mallocs = 0, fail_malloc = 0, copies = 0, fail_copy = 0, held = 0;
+int64_t mallocs = 0, fail_malloc = 0, copies = 0, fail_copy = 0, uploaded = 0, held = 0;
 int64_t news = 0, fail_new = 0;
 constexpr int kOutOfMemory = 2, kInvalid = 1;
 
@@ -34,6 +34,7 @@ void stub_fail_copy(int64_t n) { copies = 0, fail_copy = n; }
 void stub_fail_new(int64_t n) { news = 0, fail_new = n; }
 int64_t stub_mallocs() { return mallocs; }
 int64_t stub_copies() { return copies; }
+int64_t stub_uploaded() { return uploaded; }   // bytes, synchronous copies
 int64_t stub_news() { return news; }
 int64_t stub_held() { return held; }   // device allocations not freed
 
@@ -57,7 +58,10 @@ int hipHostFree(void* p) {
   std::free(p);
   return 0;
 }
-int hipMemcpy(void* d, const void* s, size_t n, int kind) { return ++copies == fail_copy ? kInvalid : copy(d, s, n, kind); }
+int hipMemcpy(void* d, const void* s, size_t n, int kind) {
+  uploaded += kind == 1 ? int64_t(n) : 0;
+  return ++copies == fail_copy ? kInvalid : copy(d, s, n, kind);
+}
 int hipMemcpyAsync(void* d, const void* s, size_t n, int kind, void*) { return copy(d, s, n, kind); }
 int hipMemset(void* d, int v, size_t n) {
   std::memset(d, v, n);

@@ -63,6 +63,12 @@ def test_viscosity_that_failed_half_way_is_not_used(stub, case):
     that need it say that none is set.  One that fails before leaves the old one in use."""
     run(stub, "half_way", case)
 
+def test_uniform_leaf_uploads_no_cell_tables(stub):
+    """No kernel reads cell or block tables of a uniform leaf; building and uploading them was three quarters of its
+    set-up.  What it does upload is the constrained dofs (8 bytes each), the pressure lattice (4 bytes a point), the
+    cells whose mean a coarser cell takes (8 x 4 bytes) and the tables of the two smallest levels."""
+    run(stub, "uniform_tables", "uniform")
+
 
 # ---------------------------------------------------- the process with the stub
 
@@ -71,7 +77,7 @@ class Child:
         import numpy as np
         self.np = np
         self.hip = C.CDLL(stub, mode=C.RTLD_GLOBAL)   # before the library: found first
-        for f in ("stub_mallocs", "stub_copies", "stub_news", "stub_held"):
+        for f in ("stub_mallocs", "stub_copies", "stub_news", "stub_uploaded", "stub_held"):
             getattr(self.hip, f).restype = C.c_int64
         for f in ("stub_fail_malloc", "stub_fail_copy", "stub_fail_new"):
             getattr(self.hip, f).argtypes = [C.c_int64]
@@ -172,6 +178,17 @@ class Child:
             assert vmult() == m.OK
         self.mu[0, 0] = -1.0
         assert self.set_viscosity(s) == m.ERR_INVALID and vmult() == m.OK
+        s.close()
+
+    def uniform_tables(self):
+        self.spec = (5, "dirichlet", 1, ())
+        s = self.solver()
+        before = self.hip.stub_uploaded()
+        assert self.set_viscosity(s) == self.m.OK
+        i = s.info()
+        constrained = sum(i["n_u"]) - sum(i["n_free"])
+        bound = 8 * constrained + 4 * i["n_p"] + 4 * sum(i["n_cells"][2:]) + 128 * 1024
+        assert self.hip.stub_uploaded() - before <= bound
         s.close()
 
     def ready(self):
