@@ -581,26 +581,29 @@ def main():
     times[("f64", "warm")] = timed(op_step("f64", False), sub, 1) / (REPS * sub)
     times[("f32", "cold")] = timed(op_step("f32", True), sub, 1) / (REPS * sub)
     times[("f32", "warm")] = timed(op_step("f32", False), sub, 1) / (REPS * sub)
-    # the cell loop alone (mfgmg_vmult_add: one brick-kernel launch per call)
+    # the accumulating form (mfgmg_vmult_add: the same kernels, adding to y)
     cell_loop = {p: timed(op_step(p, True, add=True), sub, 1) / (REPS * sub) for p in ("f64", "f32")}
 
     flops = FLOP_PER_CELL * ncell
 
     def roof(prec, peak, extra=None):
-        """Roofline of one operator application (brick kernel + halo-add
-        kernel, HIP events on the stream they are launched on), cold."""
+        """Roofline of one operator application (HIP events on the stream
+        its kernels are launched on), cold; cell_loop_*: the accumulating form."""
         call = times[(prec, "cold")]
         word = 8 if prec == "f64" else 4
         alg_bytes = 2 * word * n + word * ncell        # read x, write y, cell viscosity
         ach = flops / call / 1e12
         tr = measured_traffic(level, prec)
-        # brick shape of the level (8 x 8 x 4 cells from 64 per edge up, 8 x 4 x 4 below)
-        tname = f"{'double' if prec == 'f64' else 'float'}, 8, {8 if (1 << level) >= 64 else 4}, 4"
+        # bricks of 8 x 8 x 4 cells from 64 per edge up to 256, in FP64 of 8 x 4 x 4 at 32; the owner kernel elsewhere
+        edge = 1 << level
+        tname = f"{'double' if prec == 'f64' else 'float'}, 8, {8 if edge >= 64 else 4}, 4"
+        bricks = (32 if prec == "f64" else 64) <= edge <= 256
         # 3.4 (FP64) and 6.8 (FP32) flop/B, below the vector ridge of 9.8: bound by HBM
         out = {"bound": "hbm", "achieved": round(alg_bytes / call / 1e9, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                "frac": round(alg_bytes / call / 1e9 / PEAK_HBM_GBS, 4), "traffic": tr["bytes"] if tr else None,
                "tflops": round(ach, 3), "alu_frac": round(ach / peak, 4),
-               "kernel": f"k_vmult_brick<{tname}> + k_brick_halo_add<{tname}> (one mfgmg_vmult)",
+               "kernel": (f"k_vmult_brick<{tname}> + k_brick_halo_add<{tname}>" if bricks else "k_owner")
+               + " (one mfgmg_vmult)",
                "call_us": round(call * 1e6, 2), "cell_loop_us": round(cell_loop[prec] * 1e6, 2),
                "cell_loop_frac": round(alg_bytes / cell_loop[prec] / 1e9 / PEAK_HBM_GBS, 4),
                "flop_per_launch": flops, "alg_bytes_per_launch": alg_bytes,

@@ -63,8 +63,6 @@ __device__ __forceinline__ int split_index(int l) {
   return (l & 1) ? (B + 1) + (l >> 1) : (l >> 1);
 }
 
-// ACC: nodes inside the brick are added to y (y += A x); otherwise stored
-// (the caller initialised y to zero on free nodes)
 // Halo slot of brick b: the box [NZ][NY][3 NX] (x fastest, node-major; only
 // the rows of the high y and z faces are used), then the low and the high x
 // planes packed [NZ][NY][3].  The x planes hold one node per box row, so in
@@ -98,7 +96,8 @@ constexpr int64_t halo_buffer_words(int64_t n) {
 // A thread holds its cell's 81 values and turns them into the 81 results in
 // place (cellop::apply_cell): 126 VGPRs in FP32 (four waves per SIMD; three
 // when accumulating, whose old values need more) and 233 in FP64 (two waves
-// per SIMD).
+// per SIMD), as the compiler counts them; a kernel trace shows half of what is
+// allocated in steps of eight (64 and 120).
 template <typename T, bool ACC>
 constexpr int brick_waves_per_simd() {
   return sizeof(T) == 4 ? (ACC ? 3 : 4) : 2;
@@ -108,6 +107,8 @@ constexpr int brick_waves_per_simd() {
 // share a CU's LDS, with half a row's accesses on shared banks
 constexpr int kBrickRowPitch = 20;
 
+// ACC: y += A x on free nodes; otherwise every node is stored (nothing is
+// expected in y)
 template <typename T, int BX, int BY, int BZ, bool ACC>
 __global__ __launch_bounds__(BX * BY * BZ, (brick_waves_per_simd<T, ACC>())) void k_vmult_brick(
     int n, const T* __restrict__ mu, const T* __restrict__ x, T* __restrict__ y, T* __restrict__ halo) {

@@ -613,7 +613,7 @@ __global__ void k_invert_diag_general(int64_t nn, const uint8_t* __restrict__ cm
 template <typename T>
 __global__ void k_cheb_init0(int64_t n, const T* __restrict__ b, const T* __restrict__ minv, T* __restrict__ r,
                              T* __restrict__ d, T* __restrict__ x, T it) {
-  // XCD-contiguous ranges: t was just written by the operator in the same order
+  // XCD-contiguous ranges: the operator reads d next, in the same order
   for (int64_t i = brick::xcd_order(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x; i < n;
        i += int64_t(gridDim.x) * blockDim.x) {
     const T bi = b[i];
@@ -659,8 +659,7 @@ __global__ void k_cheb_step(int64_t n, const T* __restrict__ t, const T* __restr
 // exact arithmetic), so r is never stored and the operator is applied to x.
 // x0 = 0: d = (1/theta) M b, x = d; first step from a given x: t = A x,
 // d = (1/theta) M (b - t), x += d; later steps: d = alpha d + beta M (b - t),
-// x += d.  cmask (general levels, else null): the constrained components of
-// each node, whose t is not read: there A x = x (identity rows).
+// x += d.
 template <typename T>
 __global__ void k_chebx_init0(int64_t n, const T* __restrict__ b, const T* __restrict__ minv, T* __restrict__ d,
                               T* __restrict__ x, T it) {
@@ -671,9 +670,9 @@ __global__ void k_chebx_init0(int64_t n, const T* __restrict__ b, const T* __res
     x[i] = di;
   }
 }
-// cmask: t is not read on constrained dofs, whose rows are identities.  LAST: d
-// is not stored, one of seven streams of a memory-bound kernel (64^3 FP64 49 ->
-// 43 us).
+// cmask (general levels, else null): the constrained components of each node,
+// whose t is not used: there A x = x (identity rows).  LAST: d is not stored, one
+// of seven streams of a memory-bound kernel (64^3 FP64 49 -> 43 us).
 template <typename T, bool LAST>
 __global__ void k_chebx_step(int64_t n, const T* __restrict__ b, const T* __restrict__ t, const T* __restrict__ minv,
                              T* __restrict__ d, T* __restrict__ x, T alpha, T beta, const uint8_t* __restrict__ cmask) {
@@ -1110,8 +1109,8 @@ __global__ __launch_bounds__(kBlock) void k_restrict_z(int nc, const T* __restri
 // one size, stored in the general order, component c fixed on the two faces
 // normal to axis c only; as gathers over the transfer matrix (Morton order) the
 // restriction from 32^3 took 18.2 us FP64 (13.7), the prolongation (8 x 8 x 8
-// fine nodes a workgroup) 27.9 us (12.6).  Without a map the prolongation stays
-// with k_prolong_rows (4.1 to 6.8 us up to 32^3).
+// fine nodes a workgroup) 27.9 us (12.6).  The prolongation is for such levels
+// only; the others keep k_prolong_rows (4.1 to 6.8 us up to 32^3).
 constexpr int kTileMaxCoarse = 16;
 template <bool MAP>
 __device__ __forceinline__ bool tile_free(int m, int X, int Y, int Z, int q) {
@@ -1195,7 +1194,7 @@ __global__ __launch_bounds__(256) void k_restrict_tile(int nc, const T* __restri
   xc[tile_entry<MAP>(nodec, mc, X, Y, Z, e % 3)] = tile_free<MAP>(mc, X, Y, Z, e % 3) ? s : T(0);
 }
 
-template <typename T, bool MAP>
+template <typename T>
 __global__ __launch_bounds__(256) void k_prolong_tile(int nc, const T* __restrict__ xc, T* __restrict__ xf, bool add,
                                                       const int32_t* __restrict__ nodef,
                                                       const int32_t* __restrict__ nodec) {
@@ -1210,17 +1209,17 @@ __global__ __launch_bounds__(256) void k_prolong_tile(int nc, const T* __restric
     const int e = threadIdx.x + 256 * k, q = e % 3;
     const int X = F * bx + e % RF / 3, Y = F * by + e / RF % F, Z = F * bz + e / (RF * F);
     const bool in = X < mf && Y < mf && Z < mf;
-    at[k] = in ? tile_entry<MAP>(nodef, mf, X, Y, Z, q) : -1;
+    at[k] = in ? tile_entry<true>(nodef, mf, X, Y, Z, q) : -1;
     old[k] = add && in ? xf[at[k]] : T(0);
     // a fixed component receives nothing: its row is marked by the complement
-    if (in && !tile_free<MAP>(mf, X, Y, Z, q)) at[k] = -2 - at[k];
+    if (in && !tile_free<true>(mf, X, Y, Z, q)) at[k] = -2 - at[k];
   }
 #pragma unroll
   for (int k = 0; k < (C * C * RC + 255) / 256; ++k) {
     const int e = threadIdx.x + 256 * k, q = e % 3;
     const int X = F / 2 * bx + e % RC / 3, Y = F / 2 * by + e / RC % C, Z = F / 2 * bz + e / (RC * C);
-    const bool in = e < C * C * RC && tile_free<MAP>(mc, X, Y, Z, q);
-    const T v = xc[in ? tile_entry<MAP>(nodec, mc, X, Y, Z, q) : 0];
+    const bool in = e < C * C * RC && tile_free<true>(mc, X, Y, Z, q);
+    const T v = xc[in ? tile_entry<true>(nodec, mc, X, Y, Z, q) : 0];
     if (e < C * C * RC) sc[e] = in ? v : T(0);
   }
   __syncthreads();
@@ -2670,7 +2669,11 @@ void launch_brick(const DevLevel& L, const T* x, T* y, T* halo, bool init, hipSt
 }
 
 // 2 x 2 x 2 bricks up to 16^3 cells, 4 x 2 x 2 beyond (both measured, see
-// owner_kernel.h)
+// owner_kernel.h).  Above 256 cells per edge, where 32-bit lattice indices end and
+// with them the brick kernel, the plain operator runs here with 64-bit ones,
+// redundant cells and all: 264^3 4.2 / 7.0 ms FP32 / FP64, 512^3 28 / 50 ms, where
+// a thread per cell component with atomics into cleared output took 21.5 / 35 and
+// 161 / 285 ms.
 template <owner::Op OP, typename T>
 void launch_owner(const DevLevel& L, const T* x, const T* b, const T* minv, T* d, T* y, double alpha, double beta,
                   double it0, hipStream_t s) {
@@ -3328,7 +3331,7 @@ void launch_prolong_level(const DevLevel& F, const DevLevel& Cc, const int64_t* 
   }
   if (tile_pair(F, Cc)) {
     const int nt = int(4 * Cc.grid_edge + 8) / 8;
-    k_prolong_tile<T, true><<<unsigned(nt * nt * nt), 256, 0, s>>>(int(Cc.grid_edge), xc, xf, add, F.grid_node,
+    k_prolong_tile<T><<<unsigned(nt * nt * nt), 256, 0, s>>>(int(Cc.grid_edge), xc, xf, add, F.grid_node,
                                                                    Cc.grid_node);
     return;
   }
