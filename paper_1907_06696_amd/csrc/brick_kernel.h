@@ -96,8 +96,8 @@ constexpr int64_t halo_buffer_words(int64_t n) {
 // A thread holds its cell's 81 values and turns them into the 81 results in
 // place (cellop::apply_cell): 126 VGPRs in FP32 (four waves per SIMD; three
 // when accumulating, whose old values need more) and 233 in FP64 (two waves
-// per SIMD), as the compiler counts them; a kernel trace shows half of what is
-// allocated in steps of eight (64 and 120).
+// per SIMD), as the compiler counts them; a kernel trace's column shows about
+// half of that (64 and 120).
 template <typename T, bool ACC>
 constexpr int brick_waves_per_simd() {
   return sizeof(T) == 4 ? (ACC ? 3 : 4) : 2;

@@ -25,8 +25,8 @@
 // contractions, halo kernel and update kernel: 32^3 95 -> 53 us, 16^3 25 -> 13
 // us, 8^3 17 -> 9 us, 4^3 16 -> 9 us.  The small levels are bound by that
 // chain, the brick by LDS and vector operations alike (per wave some 120 LDS
-// reads and 1000 operations of which half are indices; 77 registers hold a
-// plane), the halo kernel by memory (5.5 TB/s).
+// reads and 1000 operations of which half are indices; 84 registers hold a
+// plane, 77 in the fused kernel), the halo kernel by memory (5.5 TB/s).
 #pragma once
 
 #include <hip/hip_runtime.h>
