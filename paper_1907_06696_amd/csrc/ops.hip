@@ -698,9 +698,12 @@ __global__ void k_chebx_step(int64_t n, const T* __restrict__ b, const T* __rest
 // of P up to 27 coarse ones): the lanes of a group read consecutive entries
 // (coalesced column and weight loads, G gathers in flight per row) and
 // reduce with shuffles inside the group.  Rows of P are bound by the chain row
-// pointer, entry, coarse value: two lanes with four entries in flight each
-// (leaf of the adaptive 32^3 + 2 workload, FP32: four lanes with one entry at a
-// time 265 us, two with four 168, one with eight 195).
+// pointer, entry, coarse value: two lanes with two entries in flight each (leaf
+// of the adaptive 32^3 + 2 workload, FP32: four lanes with one entry at a time 265
+// us, two with four 168, one with eight 195, two with two 157).  More entries in
+// flight lose where rows are short, first in FP64: 32^3 + 1 leaf FP64 20.0 us with
+// one entry at a time, 20.8 with four, 18.0 with two; 32^3 + 2 (1/27 refined), level 6: 10.8, 11.7
+// and 9.8.
 template <int G, typename T>
 __device__ __forceinline__ T group_sum(T v) {
 #pragma unroll
@@ -716,7 +719,7 @@ __global__ __launch_bounds__(kBlock) void k_prolong(int64_t nf, const int64_t* _
                                                     const int32_t* __restrict__ col, const W* __restrict__ w,
                                                     const T* __restrict__ xc, T* __restrict__ xf, bool add,
                                                     const uint8_t* __restrict__ cmf, const uint8_t* __restrict__ cmc) {
-  constexpr int U = 4;   // entries of a row in flight a lane
+  constexpr int U = 2;   // entries of a row in flight a lane
   const int sub = int(threadIdx.x) % G;
   for (int64_t f = (blockIdx.x * int64_t(blockDim.x) + threadIdx.x) / G; f < nf;
        f += int64_t(gridDim.x) * (blockDim.x / G)) {
